@@ -1080,30 +1080,151 @@ static int obs_pass_count(const P& op)
     return diag + (int)op.oc.size();
 }
 
-template <typename T, typename P>
-static hipError_t obs_passes(sv_state st, const P& op, double* partials, int* count)
+// The terms of one k_obs_tile pass: off-diagonal terms are taken in order
+// while the union of their xmasks (and the coalescing bits) fits the tile,
+// then diagonal terms [d0, d1) of the plan.
+struct ObsTileBuild {
+    ObsTilePass ps;
+    uint64_t Q;               // tile qubits
+    int term[kObsTileOff];    // plan indices of the off-diagonal terms taken
+    int n_off;
+};
+
+template <typename P>
+static void obs_tile_fill(int n, const P& op, size_t d0, size_t d1, ObsTileBuild& b)
+{
+    ObsTilePass& ps = b.ps;
+    memset(&ps, 0, sizeof ps);
+    ps.tq = std::min(n, kObsTileBits);
+    for (int q = 0; q < n && __builtin_popcountll(b.Q) < ps.tq; ++q) b.Q |= 1ull << q;
+    int local[SV_MAX_QUBITS], k = 0;
+    for (int q = 0; q < n; ++q)
+        if ((b.Q >> q) & 1) {
+            ps.q[k] = (int8_t)q;
+            local[q] = k++;
+        }
+    auto to_local = [&](uint64_t m) {
+        uint32_t l = 0;
+        for (m &= b.Q; m; m &= m - 1) l |= 1u << local[__builtin_ctzll(m)];
+        return l;
+    };
+    // off-diagonal terms, grouped by xmask (first appearance order)
+    char placed[kObsTileOff] = {};
+    for (int i = 0; i < b.n_off; ++i) {
+        if (placed[i]) continue;
+        const uint64_t x = op.ox[b.term[i]];
+        for (int j = i; j < b.n_off; ++j) {
+            const int t = b.term[j];
+            if (placed[j] || op.ox[t] != x) continue;
+            placed[j] = 1;
+            // 2 Re(i^ny w): wr, -wi, -wr, wi for ny = 0, 1, 2, 3
+            const int ny = op.oy[t] & 3;
+            ObsOffTerm& o = ps.off[ps.n_off++];
+            o.c = (ny == 1 || ny == 2 ? -2.0 : 2.0) * op.oc[t];
+            o.z = op.oz[t] & ~b.Q;
+            o.zl = (uint16_t)to_local(op.oz[t]);
+            o.f = (uint16_t)to_local(x);
+            o.imag = (uint32_t)(ny & 1);
+            o.first = j == i;
+        }
+    }
+    // diagonal terms, sorted by the register bits of their zmask
+    constexpr int lane_bits = kObsTileBits - kObsRegBits;
+    int nd = 0;
+    for (int r = 0; r < (1 << kObsRegBits); ++r) {
+        ps.dstart[r] = (uint8_t)nd;
+        for (size_t d = d0; d < d1; ++d) {
+            const uint32_t zl = to_local(op.dz[d]);
+            if ((int)(zl >> lane_bits) != r) continue;
+            ps.diag[nd].zl = zl & ((1u << lane_bits) - 1u);
+            ps.diag[nd].z = op.dz[d] & ~b.Q;
+            ps.diag[nd++].c = op.dc[d];
+        }
+    }
+    ps.dstart[1 << kObsRegBits] = (uint8_t)nd;
+}
+
+// Whether an off-diagonal term fits a k_obs_tile pass: its xmask and the
+// coalescing bits (whole 128-byte lines) within the tile.
+static uint64_t obs_tile_low(int n, int dtype)
+{
+    return (1ull << std::min(n, dtype == SV_C128 ? 3 : 4)) - 1ull;
+}
+
+// All passes of an observable.  A closed-form diagonal part with no other
+// term, and a lone off-diagonal term, keep their own one-read kernels
+// (measured equal to one tile pass); everything else goes through k_obs_tile,
+// which reads the state once for all the terms whose xmasks fit a tile.
+// 27 qubits complex128, the Heisenberg chain with a field (52 off-diagonal
+// and 53 diagonal terms): 3 reads of the state instead of 54, 2.5 ms instead
+// of 20.7.  A term whose xmask is too
+// wide for a tile keeps the one-term kernel.  Never more passes, and so
+// never more partials, than obs_pass_count.
+template <typename T, typename P, typename Done>
+static hipError_t obs_passes_in(sv_state st, const P& op, Done& done, double* partials, int* count)
 {
     int off = 0;
     hipError_t e = hipSuccess;
     const int n = st->n;
-    if (op.diag_kind > 0) {
-        e = launch_diag_obs_partial<T>(st->data, n, op.diag_kind, op.diag_coeff, nullptr, nullptr, 0, partials + off,
-                                       st->stream);
-        off += reduce_blocks_for(1ull << n);
-    } else if (op.diag_kind == 0) {
-        for (size_t k0 = 0; k0 < op.dc.size() && e == hipSuccess; k0 += kDiagTermsPerPass) {
-            const int nt = (int)std::min<size_t>(kDiagTermsPerPass, op.dc.size() - k0);
-            e = launch_diag_obs_partial<T>(st->data, n, 0, 1.0, &op.dc[k0], &op.dz[k0], nt, partials + off,
-                                           st->stream);
-            off += reduce_blocks_for(1ull << n);
-        }
+    const size_t n_off = op.oc.size(), n_diag = op.dc.size();
+    if (op.diag_kind > 0 && n_off == 0) {
+        e = launch_diag_obs_partial<T>(st->data, n, op.diag_kind, op.diag_coeff, partials, st->stream);
+        *count = reduce_blocks_for(1ull << n);
+        return e;
     }
-    for (size_t k = 0; k < op.oc.size() && e == hipSuccess; ++k) {
-        e = launch_pauli_partial<T>(st->data, n, op.ox[k], op.oz[k], op.oy[k], op.oc[k], partials + off, st->stream);
-        off += reduce_blocks_for(1ull << (n - 1));
+    const uint64_t low = obs_tile_low(n, st->dtype);
+    const int tq = std::min(n, kObsTileBits);
+    const bool lone = n_diag == 0 && n_off == 1;
+    size_t d0 = 0;
+    for (size_t k = 0; k < n_off && e == hipSuccess; ++k) {
+        if (done[k]) continue;
+        if (lone || __builtin_popcountll(op.ox[k] | low) > tq) {
+            e = launch_pauli_partial<T>(st->data, n, op.ox[k], op.oz[k], op.oy[k], op.oc[k], partials + off,
+                                        st->stream);
+            off += reduce_blocks_for(1ull << (n - 1));
+            continue;
+        }
+        ObsTileBuild b;
+        b.Q = low;
+        b.n_off = 0;
+        for (size_t j = k; j < n_off && b.n_off < kObsTileOff; ++j) {
+            if (done[j] || __builtin_popcountll(b.Q | op.ox[j]) > tq) continue;
+            done[j] = 1;
+            b.Q |= op.ox[j];
+            b.term[b.n_off++] = (int)j;
+        }
+        const size_t d1 = std::min(n_diag, d0 + kObsTileDiag);
+        obs_tile_fill(n, op, d0, d1, b);
+        d0 = d1;
+        e = launch_obs_tile<T>(st->data, n, b.ps, partials + off, st->stream);
+        off += obs_tile_blocks(n);
+    }
+    while (d0 < n_diag && e == hipSuccess) {
+        ObsTileBuild b;
+        b.Q = 0;
+        b.n_off = 0;
+        const size_t d1 = std::min(n_diag, d0 + kObsTileDiag);
+        obs_tile_fill(n, op, d0, d1, b);
+        d0 = d1;
+        e = launch_obs_tile<T>(st->data, n, b.ps, partials + off, st->stream);
+        off += obs_tile_blocks(n);
     }
     *count = off;
     return e;
+}
+
+template <typename T>
+static hipError_t obs_passes(sv_state st, const ObsPlan& op, double* partials, int* count)
+{
+    std::vector<char> done(op.oc.size(), 0);
+    return obs_passes_in<T>(st, op, done, partials, count);
+}
+
+template <typename T>
+static hipError_t obs_passes(sv_state st, const ObsPlanFixed& op, double* partials, int* count)
+{
+    char done[kNoAllocPasses] = {};  // the plan holds no more off-diagonal terms
+    return obs_passes_in<T>(st, op, done, partials, count);
 }
 
 // Partials needed by the passes of an observable (worst case: one full

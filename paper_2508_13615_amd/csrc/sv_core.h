@@ -212,14 +212,46 @@ hipError_t launch_norm_partial(const void* psi, uint64_t n_amps, double* partial
 template <typename T>
 hipError_t launch_pauli_partial(const void* psi, int n, uint64_t xmask, uint64_t zmask, int ny,
                                 double coeff, double* partials, hipStream_t s);
-// Diagonal observable sum_k c_k (-1)^{pc(x & z_k)}; kind 1 = sum Z, 2 = sum ZZ
-// (closed forms, scaled by coeff), 0 = generic list of at most
-// kDiagTermsPerPass host terms (passed by value in the kernel arguments).
-constexpr int kDiagTermsPerPass = 32;
+// Diagonal observable in closed form, scaled by coeff: kind 1 = sum Z, 2 = sum ZZ.
 template <typename T>
-hipError_t launch_diag_obs_partial(const void* psi, int n, int kind, double coeff,
-                                   const double* hcoef, const uint64_t* hz, int nterms,
-                                   double* partials, hipStream_t s);
+hipError_t launch_diag_obs_partial(const void* psi, int n, int kind, double coeff, double* partials, hipStream_t s);
+constexpr int kDiagTermsPerPass = 32;  // generic diagonal terms per k_obs_diag_apply launch
+
+// One reduction pass over many Pauli terms (k_obs_tile): the state is read
+// once, in tiles of 2^tq amplitudes that hold every bit of the pass's xmasks,
+// and the pass's off-diagonal and diagonal terms are all taken from the tile.
+// The whole description travels in the kernel arguments.
+constexpr int kObsTileBits = 12;      // tile qubits (64 KiB complex128, 32 KiB complex64)
+constexpr int kObsTileThreads = 512;  // 2^9: the tile's top 3 bits are a thread's register bits
+constexpr int kObsRegBits = 3;
+constexpr int kObsTileOff = 48;       // off-diagonal terms per pass
+constexpr int kObsTileDiag = 64;      // diagonal terms per pass
+struct ObsOffTerm {  // one 32-byte entry: a single scalar load, fetched one term ahead
+    double c;        // 2 * coefficient with the sign of i^ny
+    uint64_t z;      // zmask outside the tile
+    uint16_t zl, f;  // zmask and xmask in local bits
+    uint32_t imag;   // 1: the term takes the imaginary part (odd number of Y)
+    uint32_t first;  // 1: first term on its xmask
+    uint32_t pad;
+};
+struct ObsDiagTerm {
+    double c;
+    uint64_t z;   // zmask outside the tile
+    uint32_t zl;  // zmask's lane bits
+    uint32_t pad;
+};
+struct ObsTilePass {
+    int32_t tq, n_off;
+    int8_t q[kObsTileBits];  // tile qubits, ascending: local bit k <-> global qubit q[k]
+    uint8_t dstart[(1 << kObsRegBits) + 1];  // diagonal terms sorted by their zmask's register bits
+    ObsOffTerm off[kObsTileOff];             // grouped by xmask
+    ObsDiagTerm diag[kObsTileDiag];
+};
+static_assert(sizeof(ObsTilePass) <= 3600, "travels in the kernel arguments");
+template <typename T>
+hipError_t launch_obs_tile(const void* psi, int n, const ObsTilePass& ps, double* partials, hipStream_t s);
+// Stage-1 partials that launch_obs_tile writes for an n-qubit state.
+int obs_tile_blocks(int n);
 // Number of stage-1 blocks (= partials written) for n_items work items.
 int reduce_blocks_for(uint64_t n_items);
 hipError_t launch_sum_partials(const double* partials, int count, double* out, hipStream_t s);
