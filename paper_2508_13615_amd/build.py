@@ -24,7 +24,7 @@ CFLAGS = ["-O3", "-std=c++17", f"--offload-arch={ARCH}", "-fPIC", "-Wall", "-Wno
 # bit of a target through a switch whose cases differ only in which array
 # elements they touch; sinking their common code would turn those into
 # dynamically indexed (scratch-resident) arrays.
-FILE_FLAGS = {"k_pass.hip": ["-mllvm", "-simplifycfg-sink-common=false"]}
+FILE_FLAGS = {"k_pass.hip": ["-mllvm", "-simplifycfg-sink-common=false", "-mllvm", "-structurizecfg-skip-uniform-regions"]}
 
 
 def _compile(src):

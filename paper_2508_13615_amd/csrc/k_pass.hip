@@ -78,6 +78,195 @@ __device__ __forceinline__ V cmul_add2(T ar_, T ai_, V a, T br_, T bi_, V b)
     return r;
 }
 
+// In-place updates of amplitudes held in registers.  The amplitudes live in
+// the same registers across the whole op loop, so an op's results must end
+// up where its inputs were.  Each block forms all but one product of every
+// result in temporaries and ends with one fused multiply-add per result that
+// reads only the old value it overwrites, so nothing has to be copied back;
+// written as plain expressions the compiler placed the results elsewhere and
+// copied every amplitude once or twice per op (32 to 64 64-bit moves beside
+// the 128 multiply-adds of a 16-amplitude complex128 op).  Four independent
+// chains per block cover the multiply-add's latency.  A block in the masked
+// mode runs under the lane mask `ok` (an op controlled by lane bits): the
+// other lanes keep their amplitudes, with no select per value.  The mask is
+// set and taken back inside the block.
+enum IpMode : int {
+    IP_UNI = 0,   // uniform coefficients (scalar registers)
+    IP_LANE = 1,  // per-lane coefficients
+    IP_MASK = 2   // uniform coefficients, on the lanes of `ok` only
+};
+#define SV_ENTER "s_mov_b64 %[sv], exec\n\ts_mov_b64 exec, %[ok]\n\t"
+#define SV_LEAVE "\n\ts_mov_b64 exec, %[sv]"
+// Instantiate BODY for the element type and mode: OUT are the in-place
+// operands, IN(C) the coefficients under constraint C.
+#define SV_IP(BODY, OUT, IN)                                                                                       \
+    if constexpr (M == IP_MASK) {                                                                                  \
+        uint64_t sv;                                                                                               \
+        if constexpr (sizeof(T) == 8)                                                                              \
+            asm(SV_ENTER BODY("v_mul_f64", "v_fma_f64") SV_LEAVE : OUT, [sv] "=&s"(sv) : IN("s"), [ok] "s"(ok));   \
+        else                                                                                                       \
+            asm(SV_ENTER BODY("v_mul_f32_e64", "v_fma_f32") SV_LEAVE                                               \
+                : OUT, [sv] "=&s"(sv)                                                                              \
+                : IN("s"), [ok] "s"(ok));                                                                          \
+    } else if constexpr (M == IP_LANE) {                                                                           \
+        if constexpr (sizeof(T) == 8) asm(BODY("v_mul_f64", "v_fma_f64") : OUT : IN("v"));                         \
+        else asm(BODY("v_mul_f32_e64", "v_fma_f32") : OUT : IN("v"));                                              \
+    } else {                                                                                                       \
+        if constexpr (sizeof(T) == 8) asm(BODY("v_mul_f64", "v_fma_f64") : OUT : IN("s"));                         \
+        else asm(BODY("v_mul_f32_e64", "v_fma_f32") : OUT : IN("s"));                                              \
+    }
+
+// Complex 2x2 (row-major, interleaved u): a, b <- u (a, b).  In single
+// precision each result is the sum of two products of complex numbers, each
+// rounded once (five instructions a component); in double precision one
+// multiply and three fused multiply-adds.
+template <typename T, int M, typename V>
+__device__ __forceinline__ void pair_ip(const T* u, V& a, V& b, uint64_t ok)
+{
+#define SV_IN(C)                                                                                                   \
+    [u0] C(u[0]), [u1] C(u[1]), [u2] C(u[2]), [u3] C(u[3]), [u4] C(u[4]), [u5] C(u[5]), [u6] C(u[6]), [u7] C(u[7])
+    T m0, m1, m2, m3;
+    if constexpr (sizeof(T) == 8) {
+#define SV_BODY(MUL, FMA)                                                                                          \
+    MUL " %[m0], -%[u1], %[ay]\n\t"                                                                                \
+    MUL " %[m1], %[u1], %[ax]\n\t"                                                                                 \
+    MUL " %[m2], %[u4], %[ax]\n\t"                                                                                 \
+    MUL " %[m3], %[u5], %[ax]\n\t"                                                                                 \
+    FMA " %[m0], %[u2], %[bx], %[m0]\n\t"                                                                          \
+    FMA " %[m1], %[u3], %[bx], %[m1]\n\t"                                                                          \
+    FMA " %[m2], -%[u5], %[ay], %[m2]\n\t"                                                                         \
+    FMA " %[m3], %[u4], %[ay], %[m3]\n\t"                                                                          \
+    FMA " %[m0], -%[u3], %[by], %[m0]\n\t"                                                                         \
+    FMA " %[m1], %[u2], %[by], %[m1]\n\t"                                                                          \
+    FMA " %[m2], -%[u7], %[by], %[m2]\n\t"                                                                         \
+    FMA " %[m3], %[u7], %[bx], %[m3]\n\t"                                                                          \
+    FMA " %[ax], %[u0], %[ax], %[m0]\n\t"                                                                          \
+    FMA " %[ay], %[u0], %[ay], %[m1]\n\t"                                                                          \
+    FMA " %[bx], %[u6], %[bx], %[m2]\n\t"                                                                          \
+    FMA " %[by], %[u6], %[by], %[m3]"
+#define SV_OUT                                                                                                     \
+    [ax] "+v"(a.x), [ay] "+v"(a.y), [bx] "+v"(b.x), [by] "+v"(b.y), [m0] "=&v"(m0), [m1] "=&v"(m1),                \
+        [m2] "=&v"(m2), [m3] "=&v"(m3)
+        SV_IP(SV_BODY, SV_OUT, SV_IN)
+#undef SV_BODY
+    } else {
+        T n0, n1, n2, n3;
+#define SV_BODY(MUL, FMA)                                                                                          \
+    "v_mul_f32 %[m0], %[u1], %[ay]\n\tv_mul_f32 %[m1], %[u1], %[ax]\n\t"                                           \
+    "v_mul_f32 %[m2], %[u5], %[ay]\n\tv_mul_f32 %[m3], %[u5], %[ax]\n\t"                                           \
+    "v_mul_f32 %[n0], %[u3], %[by]\n\tv_mul_f32 %[n1], %[u3], %[bx]\n\t"                                           \
+    "v_mul_f32 %[n2], %[u7], %[by]\n\tv_mul_f32 %[n3], %[u7], %[bx]\n\t"                                           \
+    "v_fma_f32 %[m0], %[u0], %[ax], -%[m0]\n\tv_fmac_f32 %[m1], %[u0], %[ay]\n\t"                                  \
+    "v_fma_f32 %[m2], %[u4], %[ax], -%[m2]\n\tv_fmac_f32 %[m3], %[u4], %[ay]\n\t"                                  \
+    "v_fma_f32 %[n0], %[u2], %[bx], -%[n0]\n\tv_fmac_f32 %[n1], %[u2], %[by]\n\t"                                  \
+    "v_fma_f32 %[n2], %[u6], %[bx], -%[n2]\n\tv_fmac_f32 %[n3], %[u6], %[by]\n\t"                                  \
+    "v_add_f32 %[ax], %[m0], %[n0]\n\tv_add_f32 %[ay], %[m1], %[n1]\n\t"                                           \
+    "v_add_f32 %[bx], %[m2], %[n2]\n\tv_add_f32 %[by], %[m3], %[n3]"
+#define SV_OUT8 SV_OUT, [n0] "=&v"(n0), [n1] "=&v"(n1), [n2] "=&v"(n2), [n3] "=&v"(n3)
+        SV_IP(SV_BODY, SV_OUT8, SV_IN)
+#undef SV_OUT8
+#undef SV_BODY
+    }
+#undef SV_IN
+}
+
+// Real 2x2 r: a, b <- r (a, b).  A_FIRST: a's products are the ones rounded
+// before the sum, else b's.
+template <typename T, int M, bool A_FIRST, typename V>
+__device__ __forceinline__ void pairr_ip(const T* r, V& a, V& b, uint64_t ok)
+{
+    T m0, m1, m2, m3;
+#define SV_IN(C) [r0] C(r[0]), [r1] C(r[1]), [r2] C(r[2]), [r3] C(r[3])
+    if constexpr (A_FIRST) {
+#define SV_BODY(MUL, FMA)                                                                                          \
+    MUL " %[m0], %[r0], %[ax]\n\t"                                                                                 \
+    MUL " %[m1], %[r0], %[ay]\n\t"                                                                                 \
+    MUL " %[m2], %[r2], %[ax]\n\t"                                                                                 \
+    MUL " %[m3], %[r2], %[ay]\n\t"                                                                                 \
+    FMA " %[ax], %[r1], %[bx], %[m0]\n\t"                                                                          \
+    FMA " %[ay], %[r1], %[by], %[m1]\n\t"                                                                          \
+    FMA " %[bx], %[r3], %[bx], %[m2]\n\t"                                                                          \
+    FMA " %[by], %[r3], %[by], %[m3]"
+        SV_IP(SV_BODY, SV_OUT, SV_IN)
+#undef SV_BODY
+        return;
+    }
+#define SV_BODY(MUL, FMA)                                                                                          \
+    MUL " %[m0], %[r1], %[bx]\n\t"                                                                                 \
+    MUL " %[m1], %[r1], %[by]\n\t"                                                                                 \
+    MUL " %[m2], %[r3], %[bx]\n\t"                                                                                 \
+    MUL " %[m3], %[r3], %[by]\n\t"                                                                                 \
+    FMA " %[bx], %[r2], %[ax], %[m2]\n\t"                                                                          \
+    FMA " %[by], %[r2], %[ay], %[m3]\n\t"                                                                          \
+    FMA " %[ax], %[r0], %[ax], %[m0]\n\t"                                                                          \
+    FMA " %[ay], %[r0], %[ay], %[m1]"
+    SV_IP(SV_BODY, SV_OUT, SV_IN)
+#undef SV_BODY
+#undef SV_IN
+#undef SV_OUT
+}
+
+// z <- (zr + i zi) z.  RE_FIRST: the imaginary part rounds zr z.y before the
+// sum (forward subset phases), else zi z.x.
+template <typename T, int M, bool RE_FIRST, typename V>
+__device__ __forceinline__ void phase_ip(T zr, T zi, V& z, uint64_t ok)
+{
+    T m0, m1;
+#define SV_OUT [x] "+v"(z.x), [y] "+v"(z.y), [m0] "=&v"(m0), [m1] "=&v"(m1)
+#define SV_IN(C) [zr] C(zr), [zi] C(zi)
+    if constexpr (RE_FIRST) {
+#define SV_BODY(MUL, FMA)                                                                                          \
+    MUL " %[m0], -%[zi], %[y]\n\t"                                                                                 \
+    MUL " %[m1], %[zr], %[y]\n\t"                                                                                  \
+    FMA " %[y], %[zi], %[x], %[m1]\n\t"                                                                            \
+    FMA " %[x], %[zr], %[x], %[m0]"
+        SV_IP(SV_BODY, SV_OUT, SV_IN)
+#undef SV_BODY
+    } else {
+#define SV_BODY(MUL, FMA)                                                                                          \
+    MUL " %[m0], -%[zi], %[y]\n\t"                                                                                 \
+    MUL " %[m1], %[zi], %[x]\n\t"                                                                                  \
+    FMA " %[x], %[zr], %[x], %[m0]\n\t"                                                                            \
+    FMA " %[y], %[zr], %[y], %[m1]"
+        SV_IP(SV_BODY, SV_OUT, SV_IN)
+#undef SV_BODY
+    }
+#undef SV_IN
+#undef SV_OUT
+}
+
+// a <-> b.  M: IP_UNI or IP_MASK.
+template <typename T, int M, typename V>
+__device__ __forceinline__ void swap_ip(V& a, V& b, uint64_t ok)
+{
+    if constexpr (sizeof(T) == 8) {
+        T m0, m1;
+#define SV_BODY                                                                                                    \
+    "v_mov_b64 %[m0], %[ax]\n\tv_mov_b64 %[m1], %[ay]\n\tv_mov_b64 %[ax], %[bx]\n\tv_mov_b64 %[ay], %[by]\n\t"     \
+    "v_mov_b64 %[bx], %[m0]\n\tv_mov_b64 %[by], %[m1]"
+#define SV_OUT [ax] "+v"(a.x), [ay] "+v"(a.y), [bx] "+v"(b.x), [by] "+v"(b.y), [m0] "=&v"(m0), [m1] "=&v"(m1)
+        if constexpr (M == IP_MASK) {
+            uint64_t sv;
+            asm(SV_ENTER SV_BODY SV_LEAVE : SV_OUT, [sv] "=&s"(sv) : [ok] "s"(ok));
+        } else {
+            asm(SV_BODY : SV_OUT);
+        }
+#undef SV_BODY
+#undef SV_OUT
+    } else {
+#define SV_BODY "v_swap_b32 %[ax], %[bx]\n\tv_swap_b32 %[ay], %[by]"
+#define SV_OUT [ax] "+v"(a.x), [ay] "+v"(a.y), [bx] "+v"(b.x), [by] "+v"(b.y)
+        if constexpr (M == IP_MASK) {
+            uint64_t sv;
+            asm(SV_ENTER SV_BODY SV_LEAVE : SV_OUT, [sv] "=&s"(sv) : [ok] "s"(ok));
+        } else {
+            asm(SV_BODY : SV_OUT);
+        }
+#undef SV_BODY
+#undef SV_OUT
+    }
+}
+
 __device__ __forceinline__ uint32_t ins0(uint32_t x, int p)
 {
     const uint32_t lo = x & ((1u << p) - 1u);
@@ -313,65 +502,40 @@ __device__ double block_sum_fixed(double v, double* red)
 // ---------------------------------------------------------------------------
 
 
-// Lane bits of the thread and register offsets of a layout.  The layout
-// table holds the bit values, so nothing here waits on a dependent load.
-// The table words are read whole and unconditionally (uniform scalar loads);
-// each lane then keeps the values of its own set bits by a select.  (A load
-// under the lane's bit test becomes a per-lane vector load, and the chain of
-// them, one wait each, stalled every layout change.)  A workgroup has at most
-// kMaxPassThreads threads, so only the lowest kPassLaneBits lane bits occur.
-constexpr int kPassLaneBits = 9;
-static_assert((1 << kPassLaneBits) == kMaxPassThreads, "lane bits cover the largest pass workgroup");
-
-template <int RB>
-__device__ __forceinline__ void frame_of(cptr<FLayout> L, uint32_t tid, uint32_t& tl, uint32_t* off)
+// LDS byte address of a thread's register 0 in a layout.  The table words
+// are read whole and unconditionally (uniform scalar loads); each lane then
+// keeps the values of its own set bits.  (A load under the lane's bit test
+// becomes a per-lane vector load, and the chain of them, one wait each,
+// stalled every layout change.)
+__device__ __forceinline__ uint32_t lane_addr(cptr<DLayout> L, uint32_t tid)
 {
-    const cptr<uint32_t> w = (cptr<uint32_t>)L->lane_l;  // two 16-bit entries per word
     uint32_t t = 0;
 #pragma unroll
-    for (int i = 0; i < kPassLaneBits; ++i) {
-        const uint32_t b = (w[i >> 1] >> (16 * (i & 1))) & 0xffffu;
-        t |= ((tid >> i) & 1u) ? b : 0u;
-    }
-    tl = t;
-    off[0] = 0;
-#pragma unroll
-    for (int j = 1; j < (1 << RB); ++j) off[j] = off[j & (j - 1)] | L->reg_l[__builtin_ctz(j)];
-    // The offsets are uniform.  The exchanges that use them sit under the
-    // active-thread test, and a table load moved into that branch becomes a
-    // per-lane vector load with a wait; pinning the offsets to scalar
-    // registers here keeps them scalar loads ahead of the branch.
-#pragma unroll
-    for (int j = 1; j < (1 << RB); ++j) asm volatile("" ::"s"(off[j]));
+    for (int i = 0; i < kPassLaneBits; ++i) t ^= (uint32_t)__builtin_amdgcn_sbfe((int)tid, i, 1) & L->lane_b[i];
+    return t;
 }
 
-// Global element offsets of this thread's registers in a layout.
-template <int RB>
-__device__ __forceinline__ void global_frame(cptr<FLayout> L, uint32_t tid, uint64_t tile_base, uint64_t* g)
+// Byte offset in the state of a thread's register 0 in a layout.
+__device__ __forceinline__ uint64_t lane_global(cptr<DLayout> L, uint32_t tid)
 {
-    uint64_t t = tile_base;
+    uint64_t t = 0;
 #pragma unroll
-    for (int i = 0; i < kPassLaneBits; ++i) {
-        const uint64_t b = L->lane_g[i];
-        t |= ((tid >> i) & 1u) ? b : 0ull;
-    }
-    g[0] = t;
-#pragma unroll
-    for (int j = 1; j < (1 << RB); ++j) g[j] = g[j & (j - 1)] | L->reg_g[__builtin_ctz(j)];
+    for (int i = 0; i < kPassLaneBits; ++i) t |= (uint64_t)(int64_t)(int32_t)__builtin_amdgcn_sbfe((int)tid, i, 1) & L->lane_g[i];
+    return t;
 }
 
 template <typename V, int RB>
-__device__ __forceinline__ void lds_put(V* __restrict__ lds, const V* v, uint32_t tl, const uint32_t* off)
+__device__ __forceinline__ void lds_put(char* lds, const V* v, uint32_t addr, cptr<DLayout> L)
 {
 #pragma unroll
-    for (int j = 0; j < (1 << RB); ++j) lds[swz(tl | off[j])] = v[j];
+    for (int j = 0; j < (1 << RB); ++j) *(V*)(lds + (addr ^ L->reg_b[j])) = v[j];
 }
 
 template <typename V, int RB>
-__device__ __forceinline__ void lds_get(const V* __restrict__ lds, V* v, uint32_t tl, const uint32_t* off)
+__device__ __forceinline__ void lds_get(const char* lds, V* v, uint32_t addr, cptr<DLayout> L)
 {
 #pragma unroll
-    for (int j = 0; j < (1 << RB); ++j) v[j] = lds[swz(tl | off[j])];
+    for (int j = 0; j < (1 << RB); ++j) v[j] = *(const V*)(lds + (addr ^ L->reg_b[j]));
 }
 
 #define SV_K_SWITCH(k, CALL)                                                                                       \
@@ -387,7 +551,7 @@ __device__ __forceinline__ void lds_get(const V* __restrict__ lds, V* v, uint32_
 
 // In the register routines below, an op's control mask comes in two parts
 // prepared by the host for the op's layout: `cml`, the controls on lane bits
-// (tile-local bits), selects per thread between the op's coefficients and the
+// (as thread-index bits; `tl` is the thread index), selects per thread between the op's coefficients and the
 // identity (SEL); `cmk`, the controls on register bits as register indices,
 // gives each register j a test (j & cmk) == cmk that is the same for every
 // thread (CHK).  Neither needs the layout's register offsets, which keeps the
@@ -405,17 +569,14 @@ __device__ __forceinline__ bool skip_reg(int j, uint32_t cmk)
     return false;
 }
 
-template <typename T, int RB, int K, bool CHK>
-__device__ __forceinline__ void rpair_k(typename Vec2<T>::type* v, const T* u, uint32_t cmk)
+template <typename T, int RB, int K, bool CHK, int M>
+__device__ __forceinline__ void rpair_k(typename Vec2<T>::type* v, const T* u, uint32_t cmk, uint64_t ok)
 {
 #pragma unroll
     for (int j = 0; j < (1 << RB); ++j) {
         if (j & (1 << K)) continue;
         if (CHK && skip_reg(j, cmk)) continue;
-        const int j1 = j | (1 << K);
-        const auto a = v[j], b = v[j1];
-        v[j] = cmul_add2<typename Vec2<T>::type, T>(u[0], u[1], a, u[2], u[3], b);
-        v[j1] = cmul_add2<typename Vec2<T>::type, T>(u[4], u[5], a, u[6], u[7], b);
+        pair_ip<T, M>(u, v[j], v[j | (1 << K)], ok);
     }
 }
 
@@ -427,117 +588,89 @@ __device__ __forceinline__ void rpairc_k(typename Vec2<T>::type* v, const T* u0,
 #pragma unroll
     for (int j = 0; j < (1 << RB); ++j) {
         if (j & (1 << K)) continue;
-        const int j1 = j | (1 << K);
-        const T* u = (j & (1 << KS)) ? u1 : u0;
-        const auto a = v[j], b = v[j1];
-        v[j] = cmul_add2<typename Vec2<T>::type, T>(u[0], u[1], a, u[2], u[3], b);
-        v[j1] = cmul_add2<typename Vec2<T>::type, T>(u[4], u[5], a, u[6], u[7], b);
+        pair_ip<T, IP_UNI>((j & (1 << KS)) ? u1 : u0, v[j], v[j | (1 << K)], 0);
     }
 }
 
-// Real 2x2 [[r0, r1], [r2, r3]] on register bit K.
-template <typename T, int RB, int K, bool CHK>
-__device__ __forceinline__ void rpairr_k(typename Vec2<T>::type* v, const T* r, uint32_t cmk)
+// Real 2x2 [[r0, r1], [r2, r3]] on register bit K.  In single precision with
+// 16 registers and no register-bit control, register 0's pair rounds its own
+// products first: which product is rounded decides the last bit of a result,
+// and this keeps every complex64 amplitude what it has always been (LAM:
+// lambda, whose pairs all round alike).
+template <typename T, int RB, int K, bool CHK, int M, bool LAM = false>
+__device__ __forceinline__ void rpairr_k(typename Vec2<T>::type* v, const T* r, uint32_t cmk, uint64_t ok)
+{
+    constexpr bool kFirst = sizeof(T) == 4 && RB == 4 && !CHK && !LAM;
+#pragma unroll
+    for (int j = 0; j < (1 << RB); ++j) {
+        if (j & (1 << K)) continue;
+        if (CHK && skip_reg(j, cmk)) continue;
+        if (kFirst && j == 0) pairr_ip<T, M, true>(r, v[j], v[j | (1 << K)], ok);
+        else pairr_ip<T, M, false>(r, v[j], v[j | (1 << K)], ok);
+    }
+}
+
+// Exchange of the pair on register bit K (X).
+template <typename T, int RB, int K, bool CHK, int M>
+__device__ __forceinline__ void rpairx_k(typename Vec2<T>::type* v, uint32_t cmk, uint64_t ok)
 {
 #pragma unroll
     for (int j = 0; j < (1 << RB); ++j) {
         if (j & (1 << K)) continue;
         if (CHK && skip_reg(j, cmk)) continue;
-        const int j1 = j | (1 << K);
-        const auto a = v[j], b = v[j1];
-        v[j].x = r[0] * a.x + r[1] * b.x;
-        v[j].y = r[0] * a.y + r[1] * b.y;
-        v[j1].x = r[2] * a.x + r[3] * b.x;
-        v[j1].y = r[2] * a.y + r[3] * b.y;
-    }
-}
-
-// Exchange of the pair on register bit K (X); with SEL only where `ok` holds.
-template <typename T, int RB, int K, bool CHK, bool SEL>
-__device__ __forceinline__ void rpairx_k(typename Vec2<T>::type* v, bool ok, uint32_t cmk)
-{
-#pragma unroll
-    for (int j = 0; j < (1 << RB); ++j) {
-        if (j & (1 << K)) continue;
-        if (CHK && skip_reg(j, cmk)) continue;
-        const int j1 = j | (1 << K);
-        const auto a = v[j], b = v[j1];
-        if constexpr (SEL) {
-            v[j].x = ok ? b.x : a.x;
-            v[j].y = ok ? b.y : a.y;
-            v[j1].x = ok ? a.x : b.x;
-            v[j1].y = ok ? a.y : b.y;
-        } else {
-            v[j] = b;
-            v[j1] = a;
-        }
+        swap_ip<T, M>(v[j], v[j | (1 << K)], ok);
     }
 }
 
 // Element-wise diagonal d[bit of register K].
-template <typename T, int RB, int K, bool CHK>
-__device__ __forceinline__ void rdiag_k(typename Vec2<T>::type* v, const T* d, uint32_t cmk)
+template <typename T, int RB, int K, bool CHK, int M>
+__device__ __forceinline__ void rdiag_k(typename Vec2<T>::type* v, const T* d, uint32_t cmk, uint64_t ok)
 {
 #pragma unroll
     for (int j = 0; j < (1 << RB); ++j) {
         if (CHK && skip_reg(j, cmk)) continue;
-        const T zr = (j >> K) & 1 ? d[2] : d[0], zi = (j >> K) & 1 ? d[3] : d[1];
-        const auto x = v[j];
-        v[j].x = zr * x.x - zi * x.y;
-        v[j].y = zr * x.y + zi * x.x;
+        phase_ip<T, M, false>((j >> K) & 1 ? d[2] : d[0], (j >> K) & 1 ? d[3] : d[1], v[j], ok);
     }
 }
 
-// One phase z on every register (passing the register-bit controls).
-template <typename T, int RB, bool CHK>
+// One phase z (per lane) on every register (passing the register-bit controls).
+template <typename T, int RB, bool CHK, bool RE_FIRST>
 __device__ __forceinline__ void rphase(typename Vec2<T>::type* v, T zr, T zi, uint32_t cmk)
 {
 #pragma unroll
     for (int j = 0; j < (1 << RB); ++j) {
         if (CHK && skip_reg(j, cmk)) continue;
-        const auto x = v[j];
-        v[j].x = zr * x.x - zi * x.y;
-        v[j].y = zr * x.y + zi * x.x;
+        phase_ip<T, IP_LANE, RE_FIRST>(zr, zi, v[j], 0);
     }
 }
 
-template <typename T, int RB, int KA, int KB, bool CHK, bool SEL>
-__device__ __forceinline__ void rswap_k(typename Vec2<T>::type* v, bool ok, uint32_t cmk)
+template <typename T, int RB, int KA, int KB, bool CHK, int M>
+__device__ __forceinline__ void rswap_k(typename Vec2<T>::type* v, uint32_t cmk, uint64_t ok)
 {
 #pragma unroll
     for (int j = 0; j < (1 << RB); ++j) {
         if (!(j & (1 << KA)) || (j & (1 << KB))) continue;  // j: bit a = 1, bit b = 0
         if (CHK && skip_reg(j, cmk)) continue;
-        const int j1 = j ^ (1 << KA) ^ (1 << KB);
-        const auto a = v[j], b = v[j1];
-        if constexpr (SEL) {
-            v[j].x = ok ? b.x : a.x;
-            v[j].y = ok ? b.y : a.y;
-            v[j1].x = ok ? a.x : b.x;
-            v[j1].y = ok ? a.y : b.y;
-        } else {
-            v[j] = b;
-            v[j1] = a;
-        }
+        swap_ip<T, M>(v[j], v[j ^ (1 << KA) ^ (1 << KB)], ok);
     }
 }
 
 #define SV_RB_PAIRS(X) X(0, 1) X(0, 2) X(1, 0) X(1, 2) X(2, 0) X(2, 1)
 #define SV_RB4_PAIRS(X) X(0, 3) X(1, 3) X(2, 3) X(3, 0) X(3, 1) X(3, 2)
 
-template <typename T, int RB, bool CHK, bool SEL>
-__device__ __forceinline__ void rswap(int ka, int kb, typename Vec2<T>::type* v, bool ok, uint32_t cmk)
+template <typename T, int RB, bool CHK, int M>
+__device__ __forceinline__ void rswap(int ka, int kb, typename Vec2<T>::type* v, uint32_t cmk, uint64_t ok)
 {
     switch (ka * 4 + kb) {
 #define SV_CASE(A, B)                                                                                              \
-    case A * 4 + B: rswap_k<T, RB, A, B, CHK, SEL>(v, ok, cmk); break;
+    case A * 4 + B: rswap_k<T, RB, A, B, CHK, M>(v, cmk, ok); break;
         SV_RB_PAIRS(SV_CASE)
 #undef SV_CASE
     default:
         if constexpr (RB > 3) {
             switch (ka * 4 + kb) {
 #define SV_CASE(A, B)                                                                                              \
-    case A * 4 + B: rswap_k<T, RB, A, B, CHK, SEL>(v, ok, cmk); break;
+    case A * 4 + B: rswap_k<T, RB, A, B, CHK, M>(v, cmk, ok); break;
                 SV_RB4_PAIRS(SV_CASE)
 #undef SV_CASE
             default: break;
@@ -552,14 +685,16 @@ __device__ __forceinline__ void rswap(int ka, int kb, typename Vec2<T>::type* v,
 // coefficients would claim 64 scalar registers in this switch and make the
 // compiler spill scalar registers across the whole op loop.
 // DUAL: the op acts on w as well (a reverse pass un-applies it on phi and
-// lambda): one dispatch, the coefficients read once.
-template <typename T, int RB, bool CHK, bool SEL, bool TWO, bool DUAL = false>
+// lambda): one dispatch, the coefficients read once.  M: IP_UNI, or IP_MASK
+// on the lanes of `ok`.
+template <typename T, int RB, bool CHK, int M, bool TWO, bool DUAL = false>
 __device__ __forceinline__ void reg_apply_c(typename Vec2<T>::type* v, typename Vec2<T>::type* w, const FOp& op,
-                                            cptr<T> cf, bool dagger, uint32_t tl, uint32_t cmk, bool ok, T pzr, T pzi)
+                                            cptr<T> cf, bool dagger, uint32_t tl, uint32_t cmk, uint64_t ok, T pzr,
+                                            T pzi)
 {
     switch (op.kind) {
     case FK_PAIRX: {
-#define SV_CALL(K) { rpairx_k<T, RB, K, CHK, SEL>(v, ok, cmk); if constexpr (DUAL) rpairx_k<T, RB, K, CHK, SEL>(w, ok, cmk); }
+#define SV_CALL(K) { rpairx_k<T, RB, K, CHK, M>(v, cmk, ok); if constexpr (DUAL) rpairx_k<T, RB, K, CHK, M>(w, cmk, ok); }
         SV_K_SWITCH(op.ka, SV_CALL)
 #undef SV_CALL
         break;
@@ -571,13 +706,7 @@ __device__ __forceinline__ void reg_apply_c(typename Vec2<T>::type* v, typename 
             r[1] = r[2];
             r[2] = t;
         }
-        if constexpr (SEL) {
-            r[0] = ok ? r[0] : T(1);
-            r[1] = ok ? r[1] : T(0);
-            r[2] = ok ? r[2] : T(0);
-            r[3] = ok ? r[3] : T(1);
-        }
-#define SV_CALL(K) { rpairr_k<T, RB, K, CHK>(v, r, cmk); if constexpr (DUAL) rpairr_k<T, RB, K, CHK>(w, r, cmk); }
+#define SV_CALL(K) { rpairr_k<T, RB, K, CHK, M>(v, r, cmk, ok); if constexpr (DUAL) rpairr_k<T, RB, K, CHK, M, true>(w, r, cmk, ok); }
         SV_K_SWITCH(op.ka, SV_CALL)
 #undef SV_CALL
         break;
@@ -585,48 +714,45 @@ __device__ __forceinline__ void reg_apply_c(typename Vec2<T>::type* v, typename 
     case FK_PAIR: {
         T u[8];
         load2x2<T>(cf, dagger, u);
-        if constexpr (SEL) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) u[k] = ok ? u[k] : ((k == 0 || k == 6) ? T(1) : T(0));
-        }
-#define SV_CALL(K) { rpair_k<T, RB, K, CHK>(v, u, cmk); if constexpr (DUAL) rpair_k<T, RB, K, CHK>(w, u, cmk); }
+#define SV_CALL(K) { rpair_k<T, RB, K, CHK, M>(v, u, cmk, ok); if constexpr (DUAL) rpair_k<T, RB, K, CHK, M>(w, u, cmk, ok); }
         SV_K_SWITCH(op.ka, SV_CALL)
 #undef SV_CALL
         break;
     }
     case FK_DIAG: {
         T d[4] = {(T)cf[0], (T)(dagger ? -cf[1] : cf[1]), (T)cf[2], (T)(dagger ? -cf[3] : cf[3])};
-        if constexpr (SEL) {
-            d[0] = ok ? d[0] : T(1);
-            d[1] = ok ? d[1] : T(0);
-            d[2] = ok ? d[2] : T(1);
-            d[3] = ok ? d[3] : T(0);
-        }
         if (op.ka >= 0) {
-#define SV_CALL(K) { rdiag_k<T, RB, K, CHK>(v, d, cmk); if constexpr (DUAL) rdiag_k<T, RB, K, CHK>(w, d, cmk); }
+#define SV_CALL(K) { rdiag_k<T, RB, K, CHK, M>(v, d, cmk, ok); if constexpr (DUAL) rdiag_k<T, RB, K, CHK, M>(w, d, cmk, ok); }
             SV_K_SWITCH(op.ka, SV_CALL)
 #undef SV_CALL
         } else {  // target on a lane bit: one phase for all of this thread's registers
             const bool b = (tl >> op.a) & 1u;
-            rphase<T, RB, CHK>(v, b ? d[2] : d[0], b ? d[3] : d[1], cmk);
-            if constexpr (DUAL) rphase<T, RB, CHK>(w, b ? d[2] : d[0], b ? d[3] : d[1], cmk);
+            T zr = b ? d[2] : d[0], zi = b ? d[3] : d[1];
+            if constexpr (M == IP_MASK) {
+                const bool in = (tl & op.cml) == op.cml;
+                zr = in ? zr : T(1);
+                zi = in ? zi : T(0);
+            }
+            rphase<T, RB, CHK, false>(v, zr, zi, cmk);
+            if constexpr (DUAL) rphase<T, RB, CHK, false>(w, zr, zi, cmk);
         }
         break;
     }
     case FK_PHASE: {  // the caller supplies the phase (a chain's product, or conjugated in reverse)
         T zr = pzr, zi = pzi;
-        if constexpr (SEL) {
-            zr = ok ? zr : T(1);
-            zi = ok ? zi : T(0);
+        if constexpr (M == IP_MASK) {
+            const bool in = (tl & op.cml) == op.cml;
+            zr = in ? zr : T(1);
+            zi = in ? zi : T(0);
         }
-        rphase<T, RB, CHK>(v, zr, zi, cmk);
-        if constexpr (DUAL) rphase<T, RB, CHK>(w, zr, zi, cmk);
+        rphase<T, RB, CHK, !DUAL>(v, zr, zi, cmk);
+        if constexpr (DUAL) rphase<T, RB, CHK, !DUAL>(w, zr, zi, cmk);
         break;
     }
     case FK_SWAP:
         if constexpr (TWO) {
-            rswap<T, RB, CHK, SEL>(op.ka, op.kb, v, ok, cmk);
-            if constexpr (DUAL) rswap<T, RB, CHK, SEL>(op.ka, op.kb, w, ok, cmk);
+            rswap<T, RB, CHK, M>(op.ka, op.kb, v, cmk, ok);
+            if constexpr (DUAL) rswap<T, RB, CHK, M>(op.ka, op.kb, w, cmk, ok);
         }
         break;
     default: break;
@@ -647,7 +773,7 @@ __device__ __forceinline__ void reg_pairc(typename Vec2<T>::type* v, const FOp& 
         T u[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) u[k] = s ? u1[k] : u0[k];
-#define SV_CALL(K) rpair_k<T, RB, K, false>(v, u, 0u)
+#define SV_CALL(K) rpair_k<T, RB, K, false, IP_LANE>(v, u, 0u, 0)
         SV_K_SWITCH(op.ka, SV_CALL)
 #undef SV_CALL
         return;
@@ -680,13 +806,13 @@ __device__ __forceinline__ void reg_apply(typename Vec2<T>::type* v, const FOp& 
                                           uint32_t tl, T pzr, T pzi, typename Vec2<T>::type* w = nullptr)
 {
     const uint32_t cmk = op.cmk, cml = op.cml;
-    const bool ok = (tl & cml) == cml;
     if (cml) {
-        if (cmk) reg_apply_c<T, RB, true, true, TWO, DUAL>(v, w, op, cf, dagger, tl, cmk, ok, pzr, pzi);
-        else reg_apply_c<T, RB, false, true, TWO, DUAL>(v, w, op, cf, dagger, tl, 0u, ok, pzr, pzi);
+        const uint64_t ok = __ballot((tl & cml) == cml);
+        if (cmk) reg_apply_c<T, RB, true, IP_MASK, TWO, DUAL>(v, w, op, cf, dagger, tl, cmk, ok, pzr, pzi);
+        else reg_apply_c<T, RB, false, IP_MASK, TWO, DUAL>(v, w, op, cf, dagger, tl, 0u, ok, pzr, pzi);
     } else {
-        if (cmk) reg_apply_c<T, RB, true, false, TWO, DUAL>(v, w, op, cf, dagger, tl, cmk, true, pzr, pzi);
-        else reg_apply_c<T, RB, false, false, TWO, DUAL>(v, w, op, cf, dagger, tl, 0u, true, pzr, pzi);
+        if (cmk) reg_apply_c<T, RB, true, IP_UNI, TWO, DUAL>(v, w, op, cf, dagger, tl, cmk, 0, pzr, pzi);
+        else reg_apply_c<T, RB, false, IP_UNI, TWO, DUAL>(v, w, op, cf, dagger, tl, 0u, 0, pzr, pzi);
     }
 }
 
@@ -761,7 +887,6 @@ __device__ __forceinline__ double reg_gen_inner_m(const typename Vec2<T>::type* 
                                                   const FOp& op, cptr<T> m, uint32_t tl)
 {
     const uint32_t cmk = op.cmk & ~(1u << op.ka), cml = op.cml;
-    if ((tl & cml) != cml) return 0.0;
     double r = 0.0;
     if (cmk) {
 #define SV_CALL(K) r = rgen_m_k<T, RB, K, true>(P, L, m, cmk)
@@ -772,7 +897,7 @@ __device__ __forceinline__ double reg_gen_inner_m(const typename Vec2<T>::type* 
         SV_K_SWITCH(op.ka, SV_CALL)
 #undef SV_CALL
     }
-    return r;
+    return (tl & cml) == cml ? r : 0.0;
 }
 
 template <typename T, int RB>
@@ -782,10 +907,9 @@ __device__ __forceinline__ double reg_gen_inner(const typename Vec2<T>::type* P,
     // the generator's controls exclude the target (a subset-phase op lists it)
     const uint32_t tk = op.ka >= 0 ? 1u << op.ka : 0u, tlb = op.ka >= 0 ? 0u : 1u << op.a;
     const uint32_t cmk = op.cmk & ~tk, cml = op.cml & ~tlb;
-    if ((tl & cml) != cml) return 0.0;
+    double r = 0.0;
     if (op.gen == GEN_X || op.gen == GEN_Y) {
         const bool gy = op.gen == GEN_Y;
-        double r = 0.0;
         if (cmk) {
 #define SV_CALL(K) r = rgen_pair_k<T, RB, K, true>(P, L, gy, cmk)
             SV_K_SWITCH(op.ka, SV_CALL)
@@ -795,15 +919,18 @@ __device__ __forceinline__ double reg_gen_inner(const typename Vec2<T>::type* P,
             SV_K_SWITCH(op.ka, SV_CALL)
 #undef SV_CALL
         }
-        return r;
+    } else {
+        const bool gz = op.gen == GEN_Z;
+        if (op.ka >= 0) {
+            const int ka = op.ka;
+            r = rgen_elem<T, RB, true>(P, L, gz, cmk, [&](int j) { return ((j >> ka) & 1) != 0; });
+        } else {  // the target's bit is the lane's: the sum over the registers, then its sign or weight
+            r = rgen_elem<T, RB, true>(P, L, true, cmk, [&](int) { return false; });
+            const bool b = (tl >> op.a) & 1u;
+            r = b ? (gz ? -r : r) : (gz ? r : 0.0);
+        }
     }
-    const bool gz = op.gen == GEN_Z;
-    if (op.ka >= 0) {
-        const int ka = op.ka;
-        return rgen_elem<T, RB, true>(P, L, gz, cmk, [&](int j) { return ((j >> ka) & 1) != 0; });
-    }
-    const bool b = (tl >> op.a) & 1u;
-    return rgen_elem<T, RB, true>(P, L, gz, cmk, [&](int) { return b; });
+    return (tl & cml) == cml ? r : 0.0;
 }
 
 // Sum per slot of the wave partials, in fixed wave order, to the per-tile table.
@@ -895,19 +1022,22 @@ __device__ __forceinline__ void op_fetch(const PassTables& tb, int o, OpPre& p) 
 // workloads; keeping them out of the register switch keeps its code small.
 template <typename T, int RB, typename P>
 __device__ __forceinline__ void lds_op(typename Vec2<T>::type* v, typename Vec2<T>::type* lds, const FOp& op, P coef,
-                                       bool dagger, int tq, bool active, cptr<FLayout> L)
+                                       bool dagger, int tq, bool active, uint32_t addr, cptr<DLayout> L)
 {
     using V = typename Vec2<T>::type;
-    uint32_t tl, off[1 << RB];
-    frame_of<RB>(L, threadIdx.x, tl, off);
-    if (active) lds_put<V, RB>(lds, v, tl, off);
+    if (active) lds_put<V, RB>((char*)lds, v, addr, L);
     __syncthreads();
     lds_apply<T, true, P>(lds, op, coef, dagger, tq);
     __syncthreads();
-    if (active) lds_get<V, RB>(lds, v, tl, off);
+    lds_get<V, RB>((const char*)lds, v, addr, L);
     __syncthreads();
 }
 
+// A workgroup may have more threads than a circuit's tile needs (a batch's
+// circuits share one launch shape): thread i past them repeats the work of
+// thread i mod 2^(tq - rb) on its own registers and writes nothing, so the
+// registers are never under a divergent branch, which would copy all of them
+// at its join.
 // GATED: the pass holds one-target ops with controls outside the tile, which
 // act only on the tiles that hold those bits; passes without them take a
 // kernel that does not test for it.
@@ -919,103 +1049,107 @@ __device__ __forceinline__ void item_reg_fwd(const PassTables& tb, const FCirc& 
     constexpr int R = 1 << RB;
     const int tq = cc.tq;
     const cptr<FPass> pp = as_const(tb.passes) + cc.pass_begin + pidx;
-    const cptr<FLayout> lays = as_const(tb.lays);
+    const cptr<DLayout> lays = as_const(tb.lays);
     const int op_begin = pp->op_begin, op_end = pp->op_end;
     const bool gated = GATED && pp->gated != 0;
-    const bool active = threadIdx.x < (1u << (tq - RB));
+    const uint32_t tl = threadIdx.x & ((1u << (tq - RB)) - 1u);
+    const bool active = threadIdx.x == tl;
     const uint64_t tile_base = tile_base_of(pp->free_mask, (uint64_t)tile);
-    V* const psi = (V*)cc.psi;
-    uint32_t tl;
+    char* const psi = (char*)cc.psi + tile_base * sizeof(V);
     V v[R];
     int cur = pp->lay_begin;
+    uint32_t addr = lane_addr(lays + cur, tl);
     {
-        uint32_t off[R];
-        frame_of<RB>(lays + cur, threadIdx.x, tl, off);
-    }
-#pragma unroll
-    for (int j = 0; j < R; ++j) v[j].x = v[j].y = T(0);  // threads past the tile keep zeros
-    if (active) {
-        uint64_t g[R];
-        global_frame<RB>(lays + cur, threadIdx.x, tile_base, g);
+        const uint64_t lane = lane_global(lays + cur, tl);
         if (pidx == 0) {
 #pragma unroll
-            for (int j = 0; j < R; ++j) {
-                v[j].x = g[j] == 0 ? T(1) : T(0);
-                v[j].y = T(0);
-            }
+            for (int j = 0; j < R; ++j) v[j].x = v[j].y = T(0);
+            v[0].x = (tile_base | lane) == 0 ? T(1) : T(0);
         } else {
 #pragma unroll
-            for (int j = 0; j < R; ++j) v[j] = ldg<true>(psi + g[j]);
+            for (int j = 0; j < R; ++j) v[j] = ldg<true>((const V*)(psi + lays[cur].reg_g[j] + lane));
         }
     }
     const cptr<T> coef = coef_table<T>(tb);
     OpPre nx;
     if (op_begin < op_end) op_fetch(tb, op_begin, nx);
-    for (int o = op_begin; o < op_end; ++o) {
-        OpPre p = nx;
-        if (o + 1 < op_end) op_fetch(tb, o + 1, nx);
-        if constexpr (GATED) tile_select_op(p.op, tile);
-        const FOp& op = p.op;
-        T pzr = T(1), pzi = T(0);
-        if (op.kind == FK_PHASE) {
-            // A chained group of subset phases on one local mask (kb 1): the
-            // product of the phases of the ops that act on this tile (those whose
-            // bits outside the tile the tile holds), applied once by the group's
-            // last op.  A run on target a (kb 2, the last 3): members whose
-            // other in-tile bit is a lane bit count only on the lanes holding
-            // it, so the product is per lane; it is applied once to the
-            // amplitudes holding a.
-            const cptr<double> cd = as_const(tb.coef);
-            double chr = 1.0, chi = 0.0;
-            bool any = false;
-            int e = o;
-            for (;; ++e) {
-                const FOp q = e == o ? op : ld_const(as_const(tb.ops) + e);
-                if (phase_on(q, tile)) {
-                    const uint32_t lc = q.kb >= 2 ? q.cml & ~(1u << q.a) : 0u;
-                    const bool in = (tl & lc) == lc;
-                    const double zr = cd[q.coef], zi = cd[q.coef + 1];
-                    const double r = chr * zr - chi * zi, im = chr * zi + chi * zr;
-                    chr = in ? r : chr;
-                    chi = in ? im : chi;
-                    any = true;
+    int o = op_begin;
+    while (o < op_end) {
+        // Register ops, up to the next op that goes through LDS.  This inner
+        // loop holds no divergent branch: with one inside, the compiler
+        // linearises the dispatch and keeps two copies of every amplitude
+        // across it, moving all of them on each op.
+        OpPre p;
+        bool through_lds = false;
+        while (o < op_end) {
+            p = nx;
+            const int at = o;
+            if (++o < op_end) op_fetch(tb, o, nx);
+            if (p.op.kind == FK_LAYOUT || p.op.kind == FK_QUAD) {
+                through_lds = true;
+                break;
+            }
+            if constexpr (GATED) tile_select_op(p.op, tile);
+            const FOp& op = p.op;
+            T pzr = T(1), pzi = T(0);
+            if (op.kind == FK_PHASE) {
+                // A chained group of subset phases on one local mask (kb 1): the
+                // product of the phases of the ops that act on this tile (those whose
+                // bits outside the tile the tile holds), applied once by the group's
+                // last op.  A run on target a (kb 2, the last 3): members whose
+                // other in-tile bit is a lane bit count only on the lanes holding
+                // it, so the product is per lane; it is applied once to the
+                // amplitudes holding a.
+                const cptr<double> cd = as_const(tb.coef);
+                double chr = 1.0, chi = 0.0;
+                bool any = false;
+                int e = at;
+                for (;; ++e) {
+                    const FOp q = e == at ? op : ld_const(as_const(tb.ops) + e);
+                    if (phase_on(q, tile)) {
+                        // (the target's own bit aside where it is a lane bit)
+                        const uint32_t lc = q.kb >= 2 ? (q.ka >= 0 ? q.cml : q.cml & ~(1u << q.a)) : 0u;
+                        const bool in = (tl & lc) == lc;
+                        const double zr = cd[q.coef], zi = cd[q.coef + 1];
+                        const double r = chr * zr - chi * zi, im = chr * zi + chi * zr;
+                        chr = in ? r : chr;
+                        chi = in ? im : chi;
+                        any = true;
+                    }
+                    if (q.kb != 1 && q.kb != 2) break;
                 }
-                if (q.kb != 1 && q.kb != 2) break;
+                if (e != at) {  // skip the group's other ops; refetch the next descriptor
+                    o = e + 1;
+                    if (o < op_end) op_fetch(tb, o, nx);
+                }
+                if (!any) continue;
+                if (p.op.kb >= 2) {  // a run acts on the amplitudes holding its target only
+                    p.op.cmk = p.op.ka >= 0 ? (uint8_t)(1u << p.op.ka) : (uint8_t)0;
+                    p.op.cml = p.op.ka >= 0 ? 0u : 1u << p.op.a;
+                }
+                pzr = (T)chr;
+                pzi = (T)chi;
             }
-            if (e != o) {  // skip the group's other ops; refetch the next descriptor
-                o = e;
-                if (o + 1 < op_end) op_fetch(tb, o + 1, nx);
-            }
-            if (!any) continue;
-            if (p.op.kb >= 2) {  // a run acts on the amplitudes holding its target only
-                p.op.cmk = p.op.ka >= 0 ? (uint8_t)(1u << p.op.ka) : (uint8_t)0;
-                p.op.cml = p.op.ka >= 0 ? 0u : 1u << p.op.a;
-            }
-            pzr = (T)chr;
-            pzi = (T)chi;
+            if (op.kind == FK_PAIRC) reg_pairc<T, RB>(v, op, coef + op.coef, tl);
+            else if (gated && op.kind != FK_PHASE && !op_on(op, tile)) continue;  // controls outside the tile not all 1 here
+            else reg_apply<T, RB>(v, op, coef + op.coef, false, tl, pzr, pzi);
         }
-        if (op.kind == FK_LAYOUT) {
-            if (op.a == cur) continue;
-            uint32_t off[R];
-            frame_of<RB>(lays + cur, threadIdx.x, tl, off);
-            if (active) lds_put<V, RB>(lds, v, tl, off);
+        if (!through_lds) break;
+        if (p.op.kind == FK_QUAD) {
+            lds_op<T, RB>(v, lds, p.op, coef, false, tq, active, addr, lays + cur);
+        } else if (p.op.a != cur) {
+            if (active) lds_put<V, RB>((char*)lds, v, addr, lays + cur);
+            cur = p.op.a;
+            addr = lane_addr(lays + cur, tl);
             __syncthreads();
-            cur = op.a;
-            frame_of<RB>(lays + cur, threadIdx.x, tl, off);
-            if (active) lds_get<V, RB>(lds, v, tl, off);
+            lds_get<V, RB>((const char*)lds, v, addr, lays + cur);
             __syncthreads();
-            continue;
         }
-        if (op.kind == FK_QUAD) lds_op<T, RB>(v, lds, op, coef, false, tq, active, lays + cur);
-        else if (op.kind == FK_PAIRC) reg_pairc<T, RB>(v, op, coef + op.coef, tl);
-        else if (gated && op.kind != FK_PHASE && !op_on(op, tile)) continue;  // controls outside the tile not all 1 here
-        else reg_apply<T, RB>(v, op, coef + op.coef, false, tl, pzr, pzi);
     }
     if (active) {
-        uint64_t g[R];
-        global_frame<RB>(lays + cur, threadIdx.x, tile_base, g);
+        const uint64_t lane = lane_global(lays + cur, tl);
 #pragma unroll
-        for (int j = 0; j < R; ++j) stg<true>(psi + g[j], v[j]);
+        for (int j = 0; j < R; ++j) stg<true>((V*)(psi + lays[cur].reg_g[j] + lane), v[j]);
     }
 }
 
@@ -1028,90 +1162,96 @@ __device__ __forceinline__ void item_reg_rev(const PassTables& tb, const FCirc& 
     constexpr int R = 1 << RB;
     const int tq = cc.tq;
     const cptr<FPass> pp = as_const(tb.passes) + cc.pass_begin + pidx;
-    const cptr<FLayout> lays = as_const(tb.lays);
+    const cptr<DLayout> lays = as_const(tb.lays);
     const cptr<T> coef = coef_table<T>(tb);
     const int rop_begin = pp->rop_begin, rop_end = pp->rop_end;
-    const bool active = threadIdx.x < (1u << (tq - RB));
+    const uint32_t tl = threadIdx.x & ((1u << (tq - RB)) - 1u);
+    const bool active = threadIdx.x == tl;
     const uint64_t tile_base = tile_base_of(pp->free_mask, (uint64_t)tile);
-    V* const psi = (V*)cc.psi;
-    V* const lam = (V*)cc.lam;
-    uint32_t tl;
+    char* const psi = (char*)cc.psi + tile_base * sizeof(V);
+    char* const lam = (char*)cc.lam + tile_base * sizeof(V);
     V v[R], w[R];
     int cur = pp->rlay_end;
+    uint32_t addr = lane_addr(lays + cur, tl);
     {
-        uint32_t off[R];
-        frame_of<RB>(lays + cur, threadIdx.x, tl, off);
-    }
-#pragma unroll
-    for (int j = 0; j < R; ++j) v[j].x = v[j].y = w[j].x = w[j].y = T(0);  // threads past the tile keep zeros
-    if (active) {
-        uint64_t g[R];
-        global_frame<RB>(lays + cur, threadIdx.x, tile_base, g);
+        const uint64_t lane = lane_global(lays + cur, tl);
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-            v[j] = ldg<true>(psi + g[j]);
-            w[j] = ldg<true>(lam + g[j]);
+            v[j] = ldg<true>((const V*)(psi + lays[cur].reg_g[j] + lane));
+            w[j] = ldg<true>((const V*)(lam + lays[cur].reg_g[j] + lane));
         }
     }
     int nslot = 0;
     OpPre nx;
     if (rop_begin < rop_end) op_fetch(tb, rop_end - 1, nx);
-    for (int o = rop_end - 1; o >= rop_begin; --o) {
-        OpPre p = nx;
-        if (o - 1 >= rop_begin) op_fetch(tb, o - 1, nx);
-        const FOp& op = p.op;
-        if (op.kind == FK_LAYOUT) {
-            if (op.b == cur) continue;
-            uint32_t tl2, off2[R], off[R];
-            frame_of<RB>(lays + cur, threadIdx.x, tl, off);
-            frame_of<RB>(lays + op.b, threadIdx.x, tl2, off2);
-            if (active) lds_put<V, RB>(lds, v, tl, off);
-            __syncthreads();
-            if (active) lds_get<V, RB>(lds, v, tl2, off2);
-            __syncthreads();
-            if (active) lds_put<V, RB>(lds, w, tl, off);
-            __syncthreads();
-            if (active) lds_get<V, RB>(lds, w, tl2, off2);
-            __syncthreads();
-            cur = op.b;
-            tl = tl2;
-            continue;
-        }
-        // an op with bits outside the tile acts here only if the tile holds them all
-        const bool on = op_on(op, tile);
-        if (op.slot >= 0) {
-            const double c = wave_sum(active && on ? reg_gen_inner<T, RB>(v, w, op, tl) : 0.0);
-            if ((threadIdx.x & 63) == 0) wpart[nslot * (blockDim.x >> 6) + (threadIdx.x >> 6)] = c;
-            ++nslot;
-        }
-        if (op.kind == FK_RFUSE) {
-            // the pair's first gate: its partial with B G_A B^dagger; then one un-apply of B A
-            if (op.b >= 0) {
-                const double c = wave_sum(active ? reg_gen_inner_m<T, RB>(v, w, op, coef + op.coef + 8, tl) : 0.0);
-                if ((threadIdx.x & 63) == 0) wpart[nslot * (blockDim.x >> 6) + (threadIdx.x >> 6)] = c;
+    const int nwaves = blockDim.x >> 6, wave = threadIdx.x >> 6;
+    int o = rop_end - 1;
+    while (o >= rop_begin) {
+        // Register ops, up to the next op that goes through LDS (no divergent
+        // branch in this inner loop, as in the forward pass).  Every lane
+        // stores a wave's partial: the value is uniform.
+        OpPre p;
+        bool through_lds = false;
+        while (o >= rop_begin) {
+            p = nx;
+            if (--o >= rop_begin) op_fetch(tb, o, nx);
+            if (p.op.kind == FK_LAYOUT || p.op.kind == FK_SWAP || p.op.kind == FK_QUAD) {
+                through_lds = true;
+                break;
+            }
+            const FOp& op = p.op;
+            // an op with bits outside the tile acts here only if the tile holds them all
+            const bool on = op_on(op, tile);
+            if (op.slot >= 0) {
+                double c = 0.0;
+                if (on) {
+                    c = reg_gen_inner<T, RB>(v, w, op, tl);
+                    c = wave_sum(active ? c : 0.0);
+                }
+                wpart[nslot * nwaves + wave] = c;
                 ++nslot;
             }
-            p.op.kind = FK_PAIR;
-        }
-        if (!on) continue;
-        if (op.kind == FK_SWAP || op.kind == FK_QUAD) {
-            lds_op<T, RB>(v, lds, op, coef, true, tq, active, lays + cur);
-            lds_op<T, RB>(w, lds, op, coef, true, tq, active, lays + cur);
-        } else {
+            if (op.kind == FK_RFUSE) {
+                // the pair's first gate: its partial with B G_A B^dagger; then one un-apply of B A
+                if (op.b >= 0) {
+                    const double c = reg_gen_inner_m<T, RB>(v, w, op, coef + op.coef + 8, tl);
+                    wpart[nslot * nwaves + wave] = wave_sum(active ? c : 0.0);
+                    ++nslot;
+                }
+                p.op.kind = FK_PAIR;
+            }
+            if (!on) continue;
             const T pzr = op.kind == FK_PHASE ? (T)coef[op.coef] : T(1);
             const T pzi = op.kind == FK_PHASE ? (T)-coef[op.coef + 1] : T(0);
             reg_apply<T, RB, false, true>(v, op, coef + op.coef, true, tl, pzr, pzi, w);
+        }
+        if (!through_lds) break;
+        const FOp& op = p.op;
+        if (op.kind != FK_LAYOUT) {
+            lds_op<T, RB>(v, lds, op, coef, true, tq, active, addr, lays + cur);
+            lds_op<T, RB>(w, lds, op, coef, true, tq, active, addr, lays + cur);
+        } else if (op.b != cur) {
+            const uint32_t addr2 = lane_addr(lays + op.b, tl);
+            if (active) lds_put<V, RB>((char*)lds, v, addr, lays + cur);
+            __syncthreads();
+            lds_get<V, RB>((const char*)lds, v, addr2, lays + op.b);
+            __syncthreads();
+            if (active) lds_put<V, RB>((char*)lds, w, addr, lays + cur);
+            __syncthreads();
+            lds_get<V, RB>((const char*)lds, w, addr2, lays + op.b);
+            __syncthreads();
+            cur = op.b;
+            addr = addr2;
         }
     }
     __syncthreads();  // every wave's partials are in LDS
     flush_slots(tb, cc, rop_begin, rop_end, tile, wpart);
     if (active) {
-        uint64_t g[R];
-        global_frame<RB>(lays + cur, threadIdx.x, tile_base, g);
+        const uint64_t lane = lane_global(lays + cur, tl);
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-            stg<true>(psi + g[j], v[j]);
-            stg<true>(lam + g[j], w[j]);
+            stg<true>((V*)(psi + lays[cur].reg_g[j] + lane), v[j]);
+            stg<true>((V*)(lam + lays[cur].reg_g[j] + lane), w[j]);
         }
     }
 }
@@ -1266,16 +1406,14 @@ __device__ __forceinline__ FSeg seg_of(const PassTables& tb, int64_t item)
     return ld_const(segs + lo);
 }
 
-// Target waves per SIMD, which sets the VGPR budget (512 / waves).  Forward
-// complex64 passes and 8-amplitude complex128 forward passes fit 128 VGPRs;
-// the complex128 kernels with 16 amplitudes (forward) or 2 x 8 (reverse)
-// fit 168 with a few spilled registers; complex64 reverse passes with 2 x 16
-// amplitudes need the 256 of two waves.
+// Target waves per SIMD, which sets the VGPR budget (512 / waves).  Every
+// kernel fits 128 VGPRs (complex128 with 16 amplitudes forward or 2 x 8 in
+// reverse: 108 to 113; before the in-place updates, whose results need no
+// second copy of the amplitudes, 165 and three waves).
 template <typename T, int RB, bool REV>
 constexpr int pass_waves_per_eu()
 {
-    if constexpr (sizeof(T) == 4) return REV && RB == 4 ? 2 : 4;
-    else return !REV && RB == 3 ? 4 : 3;
+    return 4;
 }
 
 template <typename T, int RB, bool GATED>

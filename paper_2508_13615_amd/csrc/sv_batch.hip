@@ -543,7 +543,7 @@ struct sv_batch_s {
     FCirc* d_circ;
     FPass* d_pass;
     FOp* d_ops;
-    FLayout* d_lays;
+    DLayout* d_lays;
     FSeg* d_segs;
     FCoefSpec* d_cspec;
     FCoefSpec* d_cfac;
@@ -1099,6 +1099,67 @@ static sv_status compile_batch(const sv_batch_circuit* circuits, int n_circuits,
     return SV_OK;
 }
 
+// The planner's layouts as the kernels read them.
+static std::vector<DLayout> device_layouts(const HostTables& H, size_t eb)
+{
+    auto slot = [&](uint32_t l) {  // LDS byte offset of tile-local index l (linear over XOR)
+        return (uint32_t)((l ^ (((l >> 4) ^ (l >> 8) ^ (l >> 12)) & ((1u << kSwzBits) - 1u))) * eb);
+    };
+    std::vector<DLayout> out(H.lays.size());
+    for (size_t k = 0; k < out.size(); ++k) {
+        const FLayout& L = H.lays[k];
+        DLayout& D = out[k];
+        memset(&D, 0, sizeof D);
+        for (int i = 0; i < kPassLaneBits; ++i) {
+            D.lane_b[i] = slot(L.lane_l[i]);
+            D.lane_g[i] = L.lane_g[i] * eb;
+        }
+        for (int j = 0; j < (1 << kMaxRegBits); ++j)
+            for (int r = 0; r < kMaxRegBits; ++r)
+                if ((j >> r) & 1) {
+                    D.reg_b[j] ^= slot(L.reg_l[r]);
+                    D.reg_g[j] |= L.reg_g[r] * eb;
+                }
+    }
+    return out;
+}
+
+// The register-tiled passes' ops with their lane bits as thread-index bits
+// (the planner's lists hold them as tile-local bits).
+static std::vector<FOp> thread_bits(const HostTables& H)
+{
+    std::vector<FOp> ops = H.fops;
+    auto rewrite = [&](int begin, int end, int lay, int lanes) {
+        for (int o = begin; o < end; ++o) {
+            FOp& f = ops[o];
+            if (f.kind == FK_LAYOUT) {
+                lay = f.a;
+                continue;
+            }
+            const FLayout& L = H.lays[lay];
+            auto lane_of = [&](int bit) {
+                for (int i = 0; i < lanes; ++i)
+                    if (L.pos[i] == bit) return i;
+                return 0;
+            };
+            uint32_t m = 0;
+            for (int i = 0; i < lanes; ++i)
+                if ((f.cml >> L.pos[i]) & 1u) m |= 1u << i;
+            f.cml = m;
+            if ((f.kind == FK_DIAG || f.kind == FK_PHASE) && f.ka < 0) f.a = lane_of(f.a);
+            if (f.kind == FK_PAIRC && f.kb < 0) f.b = lane_of(f.b);
+        }
+    };
+    for (const FCirc& c : H.circs)
+        for (int p = 0; p < c.n_pass; ++p) {
+            const FPass& fp = H.passes[c.pass_begin + p];
+            if (c.reg) rewrite(fp.op_begin, fp.op_end, fp.lay_begin, c.tq - H.reg_bits);
+            if (H.with_grad && c.rreg && fp.rop_begin != fp.op_begin)
+                rewrite(fp.rop_begin, fp.rop_end, fp.rlay_begin, c.tq - H.rreg_bits);
+        }
+    return ops;
+}
+
 // Largest dynamic LDS a workgroup of the batch uses (reverse passes hold the
 // per-slot wave partials on top of the forward layout).
 static size_t engine_lds_max(const HostTables& H, int dtype)
@@ -1183,7 +1244,6 @@ sv_status sv_batch_create(const sv_batch_circuit* circuits, int n_circuits, sv_d
     const double pass_bytes = H.pass_bytes;
     std::vector<FCirc>& circs = H.circs;
     std::vector<FPass>& passes = H.passes;
-    std::vector<FOp>& fops = H.fops;
     std::vector<FCoefSpec>& cspec = H.cspec;
     std::vector<double>& slot_scale = H.slot_scale;
     std::vector<int>& slot_param = H.slot_param;
@@ -1249,8 +1309,8 @@ sv_status sv_batch_create(const sv_batch_circuit* circuits, int n_circuits, sv_d
     std::vector<double> zeros_e(std::max(1, e_total)), zeros_p(std::max(1, n_params));
     e = dev_upload(&b->d_circ, circs);
     if (e == hipSuccess) e = dev_upload(&b->d_pass, passes);
-    if (e == hipSuccess) e = dev_upload(&b->d_ops, fops);
-    if (e == hipSuccess) e = dev_upload(&b->d_lays, H.lays);
+    if (e == hipSuccess) e = dev_upload(&b->d_ops, thread_bits(H));
+    if (e == hipSuccess) e = dev_upload(&b->d_lays, device_layouts(H, dtype == SV_C128 ? 16 : 8));
     if (e == hipSuccess) e = dev_upload(&b->d_segs, segs);
     if (e == hipSuccess) e = dev_upload(&b->d_cspec, cspec);
     if (e == hipSuccess) e = dev_upload(&b->d_cfac, H.cfac);

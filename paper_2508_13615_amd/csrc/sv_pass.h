@@ -75,7 +75,10 @@ struct FOp {
     // Register-tiled passes, for the layout the op runs in: the register bits
     // holding a and b (-1 where the bit is a lane bit; b for SWAP, QUAD and
     // FK_PAIRC), and cm split into its
-    // register bits (as register indices, cmk) and its lane bits (cml).
+    // register bits (as register indices, cmk) and its lane bits (cml).  The
+    // planner's lists hold lane bits as tile-local bits; the device's copy
+    // (thread_bits) holds them as bits of the thread index: cml, and a (DIAG,
+    // PHASE) or b (PAIRC) where ka or kb is -1.
     int8_t ka, kb;
     uint8_t cmk;
     uint32_t cml;
@@ -93,6 +96,22 @@ struct FLayout {
     uint32_t pad_;
     uint64_t lane_g[16];  // global bit of lane bit i: 1 << q[pos[i]]
     uint64_t reg_g[4];    // global bit of register bit r
+};
+
+// A layout as the kernels read it (built from the FLayout when a batch is
+// created): byte offsets ready for use.  The LDS slot of an amplitude is
+// linear over XOR in its tile-local index, so a register's LDS address is the
+// thread's own (the XOR of lane_b over the set bits of the thread index) XOR
+// reg_b: one vector instruction per access.  Forming the swizzled address
+// from the tile-local index took about nine, and made a layout change of 16
+// complex128 registers about 420 vector instructions.
+constexpr int kPassLaneBits = 9;
+static_assert((1 << kPassLaneBits) == kMaxPassThreads, "lane bits cover the largest pass workgroup");
+struct DLayout {
+    uint32_t reg_b[1 << kMaxRegBits];  // LDS byte offset of register j (XOR)
+    uint32_t lane_b[12];               // LDS byte offset of lane bit i (XOR; zero past the lane bits)
+    uint64_t lane_g[kPassLaneBits + 1];  // byte offset in the state of lane bit i (zero past the lane bits)
+    uint64_t reg_g[1 << kMaxRegBits];    // byte offset in the state of register j
 };
 
 // A pass has two op lists over the same ops: the forward list (planned for
@@ -165,7 +184,7 @@ struct PassTables {
     const FCirc* circs;
     const FPass* passes;
     const FOp* ops;
-    const FLayout* lays;
+    const DLayout* lays;
     const FSeg* segs;
     const double* coef;
     const float* coef_f;  // the same coefficients rounded to float (complex64 runs)
