@@ -1058,6 +1058,23 @@ __device__ __forceinline__ void item_reg_fwd(const PassTables& tb, const FCirc& 
     char* const psi = (char*)cc.psi + tile_base * sizeof(V);
     V v[R];
     int cur = pp->lay_begin;
+    // The amplitudes outside the pass's support are zero: a tile of them
+    // stays zero, is not worked on, and is written (as zeros) by the last
+    // pass only; a tile partly outside loads the others only.  No pass before
+    // the last writes the zeros, and none reads them.  (With a coefficient
+    // that is not finite, 0 times it is not 0: every tile is worked on.)
+    const bool sparse = *as_const(tb.full) == 0;
+    const uint64_t outside = sparse ? ~pp->support : 0ull;
+    if (tile_base & outside) {
+        if (pidx == cc.n_pass - 1 && active) {
+            const uint64_t lane = lane_global(lays + cur, tl);
+            V z;
+            z.x = z.y = T(0);
+#pragma unroll
+            for (int j = 0; j < R; ++j) stg<true>((V*)(psi + lays[cur].reg_g[j] + lane), z);
+        }
+        return;
+    }
     uint32_t addr = lane_addr(lays + cur, tl);
     {
         const uint64_t lane = lane_global(lays + cur, tl);
@@ -1065,6 +1082,14 @@ __device__ __forceinline__ void item_reg_fwd(const PassTables& tb, const FCirc& 
 #pragma unroll
             for (int j = 0; j < R; ++j) v[j].x = v[j].y = T(0);
             v[0].x = (tile_base | lane) == 0 ? T(1) : T(0);
+        } else if (outside & ~pp->free_mask & cc.all_bits) {
+            const uint64_t out_b = outside * sizeof(V);  // byte offsets, as the layout's
+            const bool in = (lane & out_b) == 0;
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                v[j].x = v[j].y = T(0);
+                if (in && (lays[cur].reg_g[j] & out_b) == 0) v[j] = ldg<true>((const V*)(psi + lays[cur].reg_g[j] + lane));
+            }
         } else {
 #pragma unroll
             for (int j = 0; j < R; ++j) v[j] = ldg<true>((const V*)(psi + lays[cur].reg_g[j] + lane));
@@ -1129,6 +1154,28 @@ __device__ __forceinline__ void item_reg_fwd(const PassTables& tb, const FCirc& 
                 }
                 pzr = (T)chr;
                 pzi = (T)chi;
+            }
+            if (op.kind == FK_PRUN) {
+                // the product of the tile's entries of the byte tables, times the thread's
+                const cptr<double> cd = as_const(tb.coef) + op.coef;
+                double zr = 1.0, zi = 0.0;
+                int off = 0;
+                for (uint32_t m = (uint32_t)op.b; m; m &= m - 1u, off += 512) {
+                    const int e = off + 2 * (int)(((uint32_t)tile >> (8 * __builtin_ctz(m))) & 255u);
+                    const double ar = cd[e], ai = cd[e + 1];
+                    const double r = zr * ar - zi * ai;
+                    zi = zr * ai + zi * ar;
+                    zr = r;
+                }
+                if (op.kb) {
+                    const double2 l = *(const double2*)(tb.coef + op.coef + off + 2 * tl);
+                    const double r = zr * l.x - zi * l.y;
+                    zi = zr * l.y + zi * l.x;
+                    zr = r;
+                }
+                pzr = (T)zr;
+                pzi = (T)zi;
+                p.op.kind = FK_PHASE;
             }
             if (op.kind == FK_PAIRC) reg_pairc<T, RB>(v, op, coef + op.coef, tl);
             else if (gated && op.kind != FK_PHASE && !op_on(op, tile)) continue;  // controls outside the tile not all 1 here
@@ -1500,7 +1547,8 @@ __device__ void mul2x2(const double* a, const double* b, double* r)
 // One thread per op: gate coefficients from the parameters, in double and
 // (if coef_f is set) rounded once to float for complex64 runs.
 __global__ void k_pass_coef(const FCoefSpec* __restrict__ spec, int n, const FCoefSpec* __restrict__ factors,
-                            const double* __restrict__ params, double* __restrict__ coef, float* __restrict__ coef_f)
+                            const double* __restrict__ params, double* __restrict__ coef, float* __restrict__ coef_f,
+                            int32_t* __restrict__ full)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -1625,16 +1673,43 @@ __global__ void k_pass_coef(const FCoefSpec* __restrict__ spec, int n, const FCo
             break;
         }
     }
+    bool finite = true;
+    for (int k = 0; k < cnt; ++k) finite = finite && isfinite(c[k]);
     if (coef_f)
-        for (int k = 0; k < cnt; ++k) coef_f[s.coef + k] = (float)c[k];
+        for (int k = 0; k < cnt; ++k) {
+            coef_f[s.coef + k] = (float)c[k];
+            finite = finite && isfinite((float)c[k]);
+        }
+    if (!finite) *full = 1;
+}
+
+// The tables of the runs of subset phases (FK_PRUN): a workgroup per table.
+__global__ void __launch_bounds__(256)
+k_pass_runs(const FRunTab* __restrict__ tabs, const FRunMember* __restrict__ members, double* __restrict__ coef)
+{
+    const FRunTab t = tabs[blockIdx.x];
+    for (int e = threadIdx.x; e < t.n; e += blockDim.x) {
+        double zr = 1.0, zi = 0.0;
+        for (int k = t.begin; k < t.end; ++k) {
+            const FRunMember m = members[k];
+            if (((uint32_t)e & m.mask) != m.mask) continue;
+            const double ar = coef[m.coef], ai = coef[m.coef + 1];
+            const double r = zr * ar - zi * ai;
+            zi = zr * ai + zi * ar;
+            zr = r;
+        }
+        coef[t.dst + 2 * e] = zr;
+        coef[t.dst + 2 * e + 1] = zi;
+    }
 }
 
 // out[k] = scale[k] * sum_{i < cnt[k]} part[off[k] + i], fixed order.
 __global__ void __launch_bounds__(256)
 k_pass_segsum(const double* __restrict__ part, const int64_t* __restrict__ off, const int* __restrict__ cnt,
-              const double* __restrict__ scale, double* __restrict__ out)
+              const double* __restrict__ scale, double* __restrict__ out, int32_t* __restrict__ clear)
 {
     __shared__ double red[4];
+    if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
     const int k = blockIdx.x;
     const double* p = part + off[k];
     double acc = 0.0;
@@ -1732,18 +1807,26 @@ hipError_t launch_pass_items(const PassTables& tb, int dtype, int mode, int64_t 
 }
 
 hipError_t launch_pass_coef(const FCoefSpec* spec, int n, const FCoefSpec* factors, const double* params,
-                            double* coef, float* coef_f, hipStream_t s)
+                            double* coef, float* coef_f, int32_t* full, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pass_coef, dim3((n + 127) / 128), dim3(128), 0, s, spec, n, factors, params, coef, coef_f);
+    hipLaunchKernelGGL(k_pass_coef, dim3((n + 127) / 128), dim3(128), 0, s, spec, n, factors, params, coef, coef_f,
+                       full);
+    return hipGetLastError();
+}
+
+hipError_t launch_pass_runs(const FRunTab* tabs, int n_tabs, const FRunMember* members, double* coef, hipStream_t s)
+{
+    if (n_tabs <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_pass_runs, dim3(n_tabs), dim3(256), 0, s, tabs, members, coef);
     return hipGetLastError();
 }
 
 hipError_t launch_pass_segsum(const double* part, const int64_t* off, const int* cnt, const double* scale, double* out,
-                              int n_seg, hipStream_t s)
+                              int n_seg, int32_t* clear, hipStream_t s)
 {
     if (n_seg <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pass_segsum, dim3(n_seg), dim3(256), 0, s, part, off, cnt, scale, out);
+    hipLaunchKernelGGL(k_pass_segsum, dim3(n_seg), dim3(256), 0, s, part, off, cnt, scale, out, clear);
     return hipGetLastError();
 }
 

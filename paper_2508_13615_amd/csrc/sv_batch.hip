@@ -548,6 +548,10 @@ struct sv_batch_s {
     FCoefSpec* d_cspec;
     FCoefSpec* d_cfac;
     int n_cspec;
+    FRunTab* d_rtabs;
+    FRunMember* d_rmembers;
+    int n_rtabs;
+    int32_t* d_full;
     double* d_coef;
     float* d_coef_f;
     double* d_epart;
@@ -593,7 +597,7 @@ void batch_release(sv_batch b)
     if (b->graph) (void)hipGraphDestroy(b->graph);
     if (b->ev_in) (void)hipEventDestroy(b->ev_in);
     if (b->ev_out) (void)hipEventDestroy(b->ev_out);
-    void* ptrs[] = {b->d_psi, b->d_lam, b->d_circ, b->d_pass, b->d_ops, b->d_lays, b->d_segs, b->d_cspec, b->d_cfac, b->d_coef, b->d_coef_f, b->d_epart, b->d_gpart, b->d_e_off, b->d_e_cnt, b->d_g_off, b->d_g_cnt,
+    void* ptrs[] = {b->d_psi, b->d_lam, b->d_circ, b->d_pass, b->d_ops, b->d_lays, b->d_segs, b->d_cspec, b->d_cfac, b->d_rtabs, b->d_rmembers, b->d_full, b->d_coef, b->d_coef_f, b->d_epart, b->d_gpart, b->d_e_off, b->d_e_cnt, b->d_g_off, b->d_g_cnt,
                     b->d_slot_scale, b->d_slot_val, b->d_csr_ptr, b->d_csr_col, b->d_params, b->d_expvals,
                     b->d_grads};
     for (void* p : ptrs)
@@ -606,7 +610,8 @@ hipError_t enqueue_run(sv_batch b)
 {
     hipStream_t s = b->stream;
     hipError_t e = launch_pass_coef(b->d_cspec, b->n_cspec, b->d_cfac, b->d_params, b->d_coef,
-                                    b->dtype == SV_C64 ? b->d_coef_f : nullptr, s);
+                                    b->dtype == SV_C64 ? b->d_coef_f : nullptr, b->d_full, s);
+    if (e == hipSuccess) e = launch_pass_runs(b->d_rtabs, b->n_rtabs, b->d_rmembers, b->d_coef, s);
     const std::vector<int64_t>& lf = b->level_first;
     for (size_t l = 0; l + 3 < lf.size() && e == hipSuccess; l += 3) {
         e = launch_pass_items(b->tb, b->dtype, PM_FWD, lf[l], lf[l + 1], b->threads, b->lds_fwd, s,
@@ -615,9 +620,11 @@ hipError_t enqueue_run(sv_batch b)
         if (e == hipSuccess)
             e = launch_pass_items(b->tb, b->dtype, PM_REV, lf[l + 2], lf[l + 3], b->rthreads, b->lds_rev, s);
     }
-    if (e == hipSuccess) e = launch_pass_segsum(b->d_epart, b->d_e_off, b->d_e_cnt, nullptr, b->d_expvals, b->n_circ, s);
+    if (e == hipSuccess) e = launch_pass_segsum(b->d_epart, b->d_e_off, b->d_e_cnt, nullptr, b->d_expvals, b->n_circ,
+                                               b->d_full, s);
     if (e == hipSuccess && b->with_grad) {
-        e = launch_pass_segsum(b->d_gpart, b->d_g_off, b->d_g_cnt, b->d_slot_scale, b->d_slot_val, b->n_slots, s);
+        e = launch_pass_segsum(b->d_gpart, b->d_g_off, b->d_g_cnt, b->d_slot_scale, b->d_slot_val, b->n_slots,
+                                                nullptr, s);
         if (e == hipSuccess) e = launch_pass_grad_csr(b->d_slot_val, b->d_csr_ptr, b->d_csr_col, b->n_params, b->d_grads, s);
     }
     return e;
@@ -879,6 +886,8 @@ static sv_status compile_batch(const sv_batch_circuit* circuits, int n_circuits,
             hi_entries = std::max(hi_entries, 1 << (tq - cb));
         }
         fc.n_tiles = 1 << (n - tq);
+        fc.all_bits = (1ull << n) - 1ull;  // n <= SV_MAX_QUBITS < 64
+        uint64_t support = 0;
         fc.n_pass = (int)pops.size();
         fc.pass_begin = (int)passes.size();
         fc.obs_kind = bc.obs_kind;
@@ -904,6 +913,10 @@ static sv_status compile_batch(const sv_batch_circuit* circuits, int n_circuits,
                     fp.q[k++] = q;
                 }
             fp.free_mask = (n >= 64 ? ~0ull : ((1ull << n) - 1ull)) & ~pq[p];
+            fp.support = support;
+            for (int i : pops[p])
+                if (!diag_gate(ops[i].gate))
+                    for (int j = ops[i].nc; j < ops[i].nc + ops[i].nt; ++j) support |= 1ull << ops[i].q[j];
             std::vector<FOp> pass_ops;
             std::vector<int> pass_src;
             for (int i : pops[p]) {
@@ -1124,14 +1137,75 @@ static std::vector<DLayout> device_layouts(const HostTables& H, size_t eb)
     return out;
 }
 
-// The register-tiled passes' ops with their lane bits as thread-index bits
-// (the planner's lists hold them as tile-local bits).
-static std::vector<FOp> thread_bits(const HostTables& H)
+// What the kernels run: the planner's op lists with the register-tiled passes'
+// lane bits as thread-index bits (the planner holds them as tile-local bits),
+// and their runs of subset phases as tables.
+struct DeviceOps {
+    std::vector<FOp> ops;
+    std::vector<FRunTab> tabs;
+    std::vector<FRunMember> members;
+    int coef_total;  // with the tables, which follow the coefficients
+};
+
+// A run of subset phases (members [begin, end) of a forward list, kb 2 .. 3)
+// as an FK_PRUN, where every member is a phase of the target and either one
+// lane bit, or bits of one byte of the tile index, or neither.  The kernel
+// then takes a few table entries per run instead of fetching every member's
+// descriptor and phase and multiplying them in (about 400 cycles of scalar
+// loads a member and wave: the 30-qubit complex64 QFT spent most of its time
+// there).
+static void run_tables(DeviceOps& D, int begin, int end, int lanes)
 {
-    std::vector<FOp> ops = H.fops;
+    FOp& head = D.ops[begin];
+    auto lane_bits = [&](const FOp& f) { return f.ka >= 0 ? f.cml : f.cml & ~(1u << f.a); };
+    if (end - begin < kMinRunTable) return;
+    for (int o = begin; o < end; ++o) {
+        const FOp& f = D.ops[o];
+        const uint32_t t = (uint32_t)f.b;
+        const bool one_byte = t == 0 || ((31 - __builtin_clz(t)) >> 3) == (__builtin_ctz(t) >> 3);
+        if (!one_byte || (t && lane_bits(f))) return;
+    }
+    uint32_t bytes = 0, lane = 0;
+    const int first = D.coef_total;
+    auto table = [&](int n, auto pick) {  // pick(f, &mask): whether f is a member
+        FRunTab tb{D.coef_total, n, (int32_t)D.members.size(), 0};
+        for (int o = begin; o < end; ++o) {
+            uint32_t m = 0;
+            if (pick(D.ops[o], &m)) D.members.push_back({D.ops[o].coef, m});
+        }
+        tb.end = (int32_t)D.members.size();
+        if (tb.end == tb.begin) return false;
+        D.tabs.push_back(tb);
+        D.coef_total += 2 * n;
+        return true;
+    };
+    for (int k = 0; k < 4; ++k)
+        if (table(256, [&](const FOp& f, uint32_t* m) {
+                *m = ((uint32_t)f.b >> (8 * k)) & 255u;
+                return *m != 0;
+            }))
+            bytes |= 1u << k;
+    // members without out-of-tile bits: on the lanes holding their lane bit, or everywhere
+    lane = table(1 << lanes, [&](const FOp& f, uint32_t* m) {
+        *m = lane_bits(f);
+        return f.b == 0;
+    });
+    head.kind = FK_PRUN;
+    head.coef = first;
+    head.b = (int32_t)bytes;
+    head.kb = (int8_t)lane;
+    head.cmk = head.ka >= 0 ? (uint8_t)(1u << head.ka) : (uint8_t)0;
+    head.cml = head.ka >= 0 ? 0u : 1u << head.a;
+}
+
+static DeviceOps device_ops(HostTables& H)
+{
+    DeviceOps D;
+    D.ops = H.fops;
+    D.coef_total = (H.coef_total + 1) & ~1;  // table entries are 16-byte loads
     auto rewrite = [&](int begin, int end, int lay, int lanes) {
         for (int o = begin; o < end; ++o) {
-            FOp& f = ops[o];
+            FOp& f = D.ops[o];
             if (f.kind == FK_LAYOUT) {
                 lay = f.a;
                 continue;
@@ -1152,12 +1226,27 @@ static std::vector<FOp> thread_bits(const HostTables& H)
     };
     for (const FCirc& c : H.circs)
         for (int p = 0; p < c.n_pass; ++p) {
-            const FPass& fp = H.passes[c.pass_begin + p];
+            FPass& fp = H.passes[c.pass_begin + p];
             if (c.reg) rewrite(fp.op_begin, fp.op_end, fp.lay_begin, c.tq - H.reg_bits);
             if (H.with_grad && c.rreg && fp.rop_begin != fp.op_begin)
                 rewrite(fp.rop_begin, fp.rop_end, fp.rlay_begin, c.tq - H.rreg_bits);
+            // runs become tables where the reverse sweep does not walk the same list
+            if (!c.reg || (H.with_grad && fp.rop_begin == fp.op_begin)) continue;
+            int w = fp.op_begin;
+            for (int o = fp.op_begin; o < fp.op_end;) {
+                int e = o + 1;
+                if (D.ops[o].kind == FK_PHASE && D.ops[o].kb == 2) {
+                    while (D.ops[e].kind == FK_PHASE && D.ops[e].kb == 2) ++e;
+                    ++e;  // the run's last member (kb 3)
+                    run_tables(D, o, e, c.tq - H.reg_bits);
+                }
+                const int keep = D.ops[o].kind == FK_PRUN ? o + 1 : e;
+                while (o < keep) D.ops[w++] = D.ops[o++];
+                o = e;
+            }
+            fp.op_end = w;
         }
-    return ops;
+    return D;
 }
 
 // Largest dynamic LDS a workgroup of the batch uses (reverse passes hold the
@@ -1237,7 +1326,8 @@ sv_status sv_batch_create(const sv_batch_circuit* circuits, int n_circuits, sv_d
         sv_status rc = compile_batch(circuits, n_circuits, dtype, opts, H);
         if (rc) return rc;
     }
-    const int with_grad = H.with_grad, threads = H.threads, n_params = H.n_params, coef_total = H.coef_total;
+    const DeviceOps dops = device_ops(H);
+    const int with_grad = H.with_grad, threads = H.threads, n_params = H.n_params, coef_total = dops.coef_total;
     const int tq_used = H.tq_used, hi_entries = H.hi_entries, e_total = H.e_total;
     const int64_t g_total = H.g_total, n_items = H.n_items;
     const size_t state_total = H.state_total;
@@ -1278,6 +1368,7 @@ sv_status sv_batch_create(const sv_batch_circuit* circuits, int n_circuits, sv_d
     b->pass_bytes = pass_bytes;
     b->psi_off = psi_off;
     b->n_cspec = (int)cspec.size();
+    b->n_rtabs = (int)dops.tabs.size();
     b->level_first = level_first;
     b->level_gated = H.level_gated;
     for (int c = 0; c < n_circuits; ++c) {
@@ -1309,7 +1400,10 @@ sv_status sv_batch_create(const sv_batch_circuit* circuits, int n_circuits, sv_d
     std::vector<double> zeros_e(std::max(1, e_total)), zeros_p(std::max(1, n_params));
     e = dev_upload(&b->d_circ, circs);
     if (e == hipSuccess) e = dev_upload(&b->d_pass, passes);
-    if (e == hipSuccess) e = dev_upload(&b->d_ops, thread_bits(H));
+    if (e == hipSuccess) e = dev_upload(&b->d_ops, dops.ops);
+    if (e == hipSuccess) e = dev_upload(&b->d_rtabs, dops.tabs);
+    if (e == hipSuccess) e = dev_upload(&b->d_rmembers, dops.members);
+    if (e == hipSuccess) e = dev_upload(&b->d_full, std::vector<int32_t>{0});
     if (e == hipSuccess) e = dev_upload(&b->d_lays, device_layouts(H, dtype == SV_C128 ? 16 : 8));
     if (e == hipSuccess) e = dev_upload(&b->d_segs, segs);
     if (e == hipSuccess) e = dev_upload(&b->d_cspec, cspec);
@@ -1342,6 +1436,7 @@ sv_status sv_batch_create(const sv_batch_circuit* circuits, int n_circuits, sv_d
     tb.segs = b->d_segs;
     tb.coef = b->d_coef;
     tb.coef_f = b->d_coef_f;
+    tb.full = b->d_full;
     tb.e_part = b->d_epart;
     tb.g_part = b->d_gpart;
     tb.n_items = n_items;

@@ -38,7 +38,24 @@ constexpr int kSwzBits = 4;
 // same as taking A's after un-applying B.
 enum FusedKind : int32_t {
     FK_PAIR = 0, FK_DIAG = 1, FK_PHASE = 2, FK_SWAP = 3, FK_QUAD = 4, FK_LAYOUT = 5, FK_PAIRR = 6, FK_PAIRX = 7,
-    FK_PAIRC = 8, FK_PAIRT = 9, FK_RFUSE = 10
+    FK_PAIRC = 8, FK_PAIRT = 9, FK_RFUSE = 10,
+    // Device lists only (device_ops): a whole run of subset phases on one
+    // target as tables (FRunTab): one table per byte of the tile index that a
+    // member's out-of-tile bits lie in, and one over the threads for members
+    // with a lane bit.  b: bit k set if byte k has a table, kb: 1 if the run
+    // has a lane table, coef: the first table (byte tables, then the lane
+    // table), cmk / cml: the target's bit.
+    FK_PRUN = 11
+};
+constexpr int kMinRunTable = 4;  // members from which a run becomes tables
+// One table of an FK_PRUN: entry e (n entries of a complex double at dst) is
+// the product of the members [begin, end) whose mask lies within e.
+struct FRunTab {
+    int32_t dst, n, begin, end;
+};
+struct FRunMember {
+    int32_t coef;   // the member's phase in the coefficient table
+    uint32_t mask;  // its bits of the table's index
 };
 // Largest packed mask of an FK_PAIRT (bits), so its table holds at most 32
 // matrices.
@@ -126,6 +143,10 @@ struct FPass {
     uint64_t free_mask;  // global bits outside the tile (the tile index is deposited into them)
     int32_t gated;       // 1 if a one-target op of the forward list has controls outside the tile
     int32_t pad_;
+    // Bits that an amplitude's index can hold when the pass begins (the
+    // targets of every earlier op that moves weight between amplitudes): the
+    // run starts from |0...0>, so every amplitude with another bit is zero.
+    uint64_t support;
 };
 
 struct FCirc {
@@ -142,6 +163,7 @@ struct FCirc {
     int32_t reg;           // 1: forward passes are register-tiled (tq >= rb); 0: every op sweeps an LDS tile
     int32_t rreg;          // the same for reverse passes (tq >= reverse rb)
     int32_t pad_;
+    uint64_t all_bits;     // 2^n - 1
 };
 
 // Items [first, first + n_tiles) are the tiles of stage `stage` of `circ`;
@@ -188,6 +210,7 @@ struct PassTables {
     const FSeg* segs;
     const double* coef;
     const float* coef_f;  // the same coefficients rounded to float (complex64 runs)
+    const int32_t* full;  // 1: some coefficient is not finite, so zero amplitudes are computed like any other
     double* e_part;
     double* g_part;
     int64_t n_items;
@@ -208,10 +231,13 @@ hipError_t pass_engine_prepare(size_t lds_bytes);
 // gated: some forward pass among the items has FPass.gated set.
 hipError_t launch_pass_items(const PassTables& tb, int dtype, int mode, int64_t item_begin, int64_t item_end,
                              int threads, size_t lds_bytes, hipStream_t s, bool gated = false);
+// Sets *full to 1 if a coefficient is not finite.
 hipError_t launch_pass_coef(const FCoefSpec* spec, int n, const FCoefSpec* factors, const double* params,
-                            double* coef, float* coef_f, hipStream_t s);
+                            double* coef, float* coef_f, int32_t* full, hipStream_t s);
+hipError_t launch_pass_runs(const FRunTab* tabs, int n_tabs, const FRunMember* members, double* coef, hipStream_t s);
+// clear (may be null): set to 0 (the flag of launch_pass_coef, after its last reader).
 hipError_t launch_pass_segsum(const double* part, const int64_t* off, const int* cnt, const double* scale, double* out,
-                              int n_seg, hipStream_t s);
+                              int n_seg, int32_t* clear, hipStream_t s);
 hipError_t launch_pass_grad_csr(const double* slot_val, const int* rowptr, const int* cols, int n_params, double* grad,
                                 hipStream_t s);
 // Dynamic LDS of a pass workgroup: tiles and address map, plus per-slot wave
