@@ -538,6 +538,32 @@ __device__ __forceinline__ void lds_get(const char* lds, V* v, uint32_t addr, cp
     for (int j = 0; j < (1 << RB); ++j) v[j] = *(const V*)(lds + (addr ^ L->reg_b[j]));
 }
 
+// Exchange of a thread's amplitudes from one layout to another through an
+// LDS buffer of half a tile: the real parts, then the imaginary parts, each
+// in 8-byte slots.  A complex128 forward workgroup of one wavefront holds a
+// 16 KiB tile, and with whole amplitudes in LDS ten of them (2.5 wavefronts
+// per SIMD) filled a CU's 160 KiB; half the buffer leaves the registers (4
+// per SIMD) as the limit.
+template <typename V, int RB>
+__device__ __forceinline__ void lds_exchange_half(char* lds, V* v, bool active, uint32_t a0, cptr<DLayout> L0,
+                                                  uint32_t a1, cptr<DLayout> L1)
+{
+    if (active)
+#pragma unroll
+        for (int j = 0; j < (1 << RB); ++j) *(double*)(lds + ((a0 ^ L0->reg_b[j]) >> 1)) = v[j].x;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < (1 << RB); ++j) v[j].x = *(const double*)(lds + ((a1 ^ L1->reg_b[j]) >> 1));
+    __syncthreads();
+    if (active)
+#pragma unroll
+        for (int j = 0; j < (1 << RB); ++j) *(double*)(lds + ((a0 ^ L0->reg_b[j]) >> 1)) = v[j].y;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < (1 << RB); ++j) v[j].y = *(const double*)(lds + ((a1 ^ L1->reg_b[j]) >> 1));
+    __syncthreads();
+}
+
 #define SV_K_SWITCH(k, CALL)                                                                                       \
     switch (k) {                                                                                                   \
     case 0: CALL(0); break;                                                                                        \
@@ -1038,6 +1064,25 @@ __device__ __forceinline__ void lds_op(typename Vec2<T>::type* v, typename Vec2<
 // thread i mod 2^(tq - rb) on its own registers and writes nothing, so the
 // registers are never under a divergent branch, which would copy all of them
 // at its join.
+// Reads [p, p + bytes) into the scalar cache, one word per 64-byte line,
+// eight lines in flight.  A pass reads each descriptor, layout and coefficient
+// once per wave; in a launch of few workgroups nobody has read them before,
+// and every op waited about 700 cycles for its coefficients to come from the
+// L2 (a 10-qubit HEA in one workgroup: 0.9 us an op).  A large launch finds
+// them cached and skips this.
+__device__ __forceinline__ void warm_lines(const void* p, int bytes)
+{
+    const cptr<uint32_t> w = as_const((const uint32_t*)p);
+    for (int o = 0; o < bytes; o += 512) {
+        uint32_t x[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[k] = w[(o + 64 * k < bytes ? o + 64 * k : o) >> 2];
+        asm volatile("" ::"s"(x[0]), "s"(x[1]), "s"(x[2]), "s"(x[3]), "s"(x[4]), "s"(x[5]), "s"(x[6]), "s"(x[7]));
+    }
+}
+// Workgroups of a launch up to which they warm the scalar cache.
+constexpr uint32_t kWarmGrid = 4096;
+
 // GATED: the pass holds one-target ops with controls outside the tile, which
 // act only on the tiles that hold those bits; passes without them take a
 // kernel that does not test for it.
@@ -1096,6 +1141,11 @@ __device__ __forceinline__ void item_reg_fwd(const PassTables& tb, const FCirc& 
         }
     }
     const cptr<T> coef = coef_table<T>(tb);
+    if (gridDim.x <= kWarmGrid) {
+        warm_lines(tb.ops + op_begin, (op_end - op_begin) * (int)sizeof(FOp));
+        warm_lines((const T*)coef + pp->wcoef_begin, (pp->wcoef_end - pp->wcoef_begin) * (int)sizeof(T));
+        warm_lines(tb.lays + pp->wlay_begin, (pp->wlay_end - pp->wlay_begin) * (int)sizeof(DLayout));
+    }
     OpPre nx;
     if (op_begin < op_end) op_fetch(tb, op_begin, nx);
     int o = op_begin;
@@ -1185,6 +1235,15 @@ __device__ __forceinline__ void item_reg_fwd(const PassTables& tb, const FCirc& 
         if (p.op.kind == FK_QUAD) {
             lds_op<T, RB>(v, lds, p.op, coef, false, tq, active, addr, lays + cur);
         } else if (p.op.a != cur) {
+            if constexpr (sizeof(T) == 8) {
+                if (tb.lds_half) {
+                    const uint32_t to = lane_addr(lays + p.op.a, tl);
+                    lds_exchange_half<V, RB>((char*)lds, v, active, addr, lays + cur, to, lays + p.op.a);
+                    cur = p.op.a;
+                    addr = to;
+                    continue;
+                }
+            }
             if (active) lds_put<V, RB>((char*)lds, v, addr, lays + cur);
             cur = p.op.a;
             addr = lane_addr(lays + cur, tl);
@@ -1229,6 +1288,11 @@ __device__ __forceinline__ void item_reg_rev(const PassTables& tb, const FCirc& 
         }
     }
     int nslot = 0;
+    if (gridDim.x <= kWarmGrid) {
+        warm_lines(tb.ops + rop_begin, (rop_end - rop_begin) * (int)sizeof(FOp));
+        warm_lines((const T*)coef + pp->wrcoef_begin, (pp->wrcoef_end - pp->wrcoef_begin) * (int)sizeof(T));
+        warm_lines(tb.lays + pp->wrlay_begin, (pp->wrlay_end - pp->wrlay_begin) * (int)sizeof(DLayout));
+    }
     OpPre nx;
     if (rop_begin < rop_end) op_fetch(tb, rop_end - 1, nx);
     const int nwaves = blockDim.x >> 6, wave = threadIdx.x >> 6;

@@ -1198,6 +1198,8 @@ static void run_tables(DeviceOps& D, int begin, int end, int lanes)
     head.cml = head.ka >= 0 ? 0u : 1u << head.a;
 }
 
+constexpr int kWarmCoefs = 1024;  // coefficients a workgroup reads ahead at most (half of the scalar cache)
+
 static DeviceOps device_ops(HostTables& H)
 {
     DeviceOps D;
@@ -1245,6 +1247,44 @@ static DeviceOps device_ops(HostTables& H)
                 o = e;
             }
             fp.op_end = w;
+        }
+    // the layouts and coefficients each list reads
+    auto span = [&](int begin, int end, int lay, int32_t* lb, int32_t* le, int32_t* cb, int32_t* ce) {
+        int lo = lay, hi = lay + 1, c0 = INT32_MAX, c1 = 0;
+        for (int o = begin; o < end; ++o) {
+            const FOp& f = D.ops[o];
+            int n = 0;
+            switch (f.kind) {
+            case FK_LAYOUT:
+                lo = std::min(lo, f.a);
+                hi = std::max(hi, f.a + 1);
+                break;
+            case FK_PAIR:
+            case FK_PAIRR: n = 8; break;
+            case FK_PAIRC:
+            case FK_RFUSE: n = 16; break;
+            case FK_DIAG: n = 4; break;
+            case FK_PHASE: n = 2; break;
+            default: break;
+            }
+            if (n) {
+                c0 = std::min(c0, f.coef);
+                c1 = std::max(c1, f.coef + n);
+            }
+        }
+        if (c0 > c1) c0 = c1 = 0;
+        *lb = lo;
+        *le = hi;
+        *cb = c0;
+        *ce = std::min(c1, c0 + kWarmCoefs);
+    };
+    for (const FCirc& c : H.circs)
+        for (int p = 0; p < c.n_pass; ++p) {
+            FPass& fp = H.passes[c.pass_begin + p];
+            if (c.reg) span(fp.op_begin, fp.op_end, fp.lay_begin, &fp.wlay_begin, &fp.wlay_end, &fp.wcoef_begin, &fp.wcoef_end);
+            if (H.with_grad && c.rreg)
+                span(fp.rop_begin, fp.rop_end, fp.rlay_begin, &fp.wrlay_begin, &fp.wrlay_end, &fp.wrcoef_begin,
+                     &fp.wrcoef_end);
         }
     return D;
 }
@@ -1447,7 +1487,12 @@ sv_status sv_batch_create(const sv_batch_circuit* circuits, int n_circuits, sv_d
     tb.reg_bits = H.reg_bits;
     tb.rreg_bits = H.rreg_bits;
     tb.lds_small = H.lds_small;
-    b->lds_fwd = pass_engine_lds_bytes(tq_used, hi_entries, with_grad, dtype, H.lds_small, 0);
+    // the forward exchange needs half a tile unless some op or circuit works on a tile in LDS
+    tb.lds_half = dtype == SV_C128 && !H.lds_small;
+    for (const FPass& fp : passes)
+        for (int o = fp.op_begin; o < fp.op_end; ++o)
+            if (dops.ops[o].kind == FK_QUAD) tb.lds_half = 0;
+    b->lds_fwd = pass_engine_lds_bytes(tq_used, hi_entries, with_grad, dtype, H.lds_small, 0) >> tb.lds_half;
     b->lds_rev = pass_engine_lds_bytes(tq_used, hi_entries, with_grad, dtype, H.lds_small, H.rthreads / 64);
     e = pass_engine_prepare(engine_lds_max(H, dtype));
     if (e != hipSuccess) {

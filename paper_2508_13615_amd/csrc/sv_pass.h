@@ -147,6 +147,11 @@ struct FPass {
     // targets of every earlier op that moves weight between amplitudes): the
     // run starts from |0...0>, so every amplitude with another bit is zero.
     uint64_t support;
+    // What a workgroup of a small launch reads into the scalar cache first:
+    // the layouts and coefficients (in doubles) of the forward and of the
+    // reverse list (device lists only).
+    int32_t wlay_begin, wlay_end, wcoef_begin, wcoef_end;
+    int32_t wrlay_begin, wrlay_end, wrcoef_begin, wrcoef_end;
 };
 
 struct FCirc {
@@ -220,6 +225,7 @@ struct PassTables {
     int32_t hi_entries;  // LDS address-map entries: max over circuits of 2^(tq - cb)
     int32_t reg_bits;    // rb of register-tiled forward passes
     int32_t rreg_bits;   // rb of register-tiled reverse passes
+    int32_t lds_half;    // 1: complex128 forward passes exchange through half a tile of LDS
     int32_t lds_small;   // 1 if some circuit takes the LDS-sweep form (tq < rb)
 };
 
