@@ -1123,7 +1123,7 @@ __device__ __forceinline__ void item_reg_fwd(const PassTables& tb, const FCirc& 
     uint32_t addr = lane_addr(lays + cur, tl);
     {
         const uint64_t lane = lane_global(lays + cur, tl);
-        if (pidx == 0) {
+        if (pidx == 0 && !cc.loaded) {
 #pragma unroll
             for (int j = 0; j < R; ++j) v[j].x = v[j].y = T(0);
             v[0].x = (tile_base | lane) == 0 ? T(1) : T(0);
@@ -1427,7 +1427,7 @@ __device__ __forceinline__ void item_lds(const PassTables& tb, const FCirc& cc, 
     __syncthreads();
     const uint32_t lomask = (1u << cb) - 1u;
     if (fwd) {
-        if (pidx == 0) {
+        if (pidx == 0 && !cc.loaded) {
             for (uint32_t l = threadIdx.x; l < na; l += blockDim.x) {
                 const uint64_t g = hi_map[l >> cb] | (l & lomask);
                 V v;
@@ -1767,6 +1767,13 @@ k_pass_runs(const FRunTab* __restrict__ tabs, const FRunMember* __restrict__ mem
     }
 }
 
+// The states a run works on (an engine on a caller's states).
+__global__ void k_pass_bind(FCirc* circ, void* psi, void* lam)
+{
+    circ->psi = psi;
+    circ->lam = lam;
+}
+
 // out[k] = scale[k] * sum_{i < cnt[k]} part[off[k] + i], fixed order.
 __global__ void __launch_bounds__(256)
 k_pass_segsum(const double* __restrict__ part, const int64_t* __restrict__ off, const int* __restrict__ cnt,
@@ -1876,6 +1883,12 @@ hipError_t launch_pass_coef(const FCoefSpec* spec, int n, const FCoefSpec* facto
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_pass_coef, dim3((n + 127) / 128), dim3(128), 0, s, spec, n, factors, params, coef, coef_f,
                        full);
+    return hipGetLastError();
+}
+
+hipError_t launch_pass_bind(FCirc* circ, void* psi, void* lam, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_pass_bind, dim3(1), dim3(1), 0, s, circ, psi, lam);
     return hipGetLastError();
 }
 

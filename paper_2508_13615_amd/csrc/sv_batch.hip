@@ -540,6 +540,7 @@ struct sv_batch_s {
     // device allocations
     void* d_psi;
     void* d_lam;
+    void* d_tables;  // one allocation for everything below
     FCirc* d_circ;
     FPass* d_pass;
     FOp* d_ops;
@@ -579,15 +580,53 @@ struct sv_batch_s {
 
 namespace {
 
-template <typename X>
-hipError_t dev_upload(X** dst, const std::vector<X>& src)
-{
-    const size_t bytes = std::max<size_t>(1, src.size()) * sizeof(X);
-    hipError_t e = hipMalloc((void**)dst, bytes);
-    if (e != hipSuccess) return e;
-    if (!src.empty()) e = hipMemcpy(*dst, src.data(), src.size() * sizeof(X), hipMemcpyHostToDevice);
-    return e;
-}
+// A batch's tables and work arrays in one device allocation.  Small tables are
+// gathered and go up in one copy, large ones go straight from where they are
+// (some thirty separate allocations and copies took most of the time of
+// creating a small batch).  The sources live until place().
+struct TableArena {
+    struct Item {
+        void** dst;
+        const void* src;  // null: a work array
+        size_t bytes, off;
+    };
+    std::vector<Item> items;
+    template <typename X>
+    void table(X** dst, const std::vector<X>& src)
+    {
+        items.push_back({(void**)dst, src.data(), src.size() * sizeof(X), 0});
+    }
+    template <typename X>
+    void array(X** dst, size_t count)
+    {
+        items.push_back({(void**)dst, nullptr, count * sizeof(X), 0});
+    }
+    hipError_t place(void** base)
+    {
+        constexpr size_t kSmall = 64 << 10;
+        auto small = [](const Item& it) { return it.src && it.bytes <= kSmall; };
+        size_t total = 0, staged = 0;
+        for (const bool want_small : {true, false}) {
+            for (Item& it : items)
+                if (small(it) == want_small) {
+                    it.off = total;
+                    total = (total + std::max<size_t>(it.bytes, 1) + 255) & ~(size_t)255;
+                }
+            if (want_small) staged = total;
+        }
+        hipError_t e = hipMalloc(base, total);
+        if (e != hipSuccess) return e;
+        std::vector<char> host(staged);
+        for (const Item& it : items) {
+            *it.dst = (char*)*base + it.off;
+            if (!it.src || !it.bytes) continue;
+            if (small(it)) memcpy(host.data() + it.off, it.src, it.bytes);
+            else if (e == hipSuccess) e = hipMemcpy(*it.dst, it.src, it.bytes, hipMemcpyHostToDevice);
+        }
+        if (e == hipSuccess && staged) e = hipMemcpy(*base, host.data(), staged, hipMemcpyHostToDevice);
+        return e;
+    }
+};
 
 void batch_release(sv_batch b)
 {
@@ -597,36 +636,49 @@ void batch_release(sv_batch b)
     if (b->graph) (void)hipGraphDestroy(b->graph);
     if (b->ev_in) (void)hipEventDestroy(b->ev_in);
     if (b->ev_out) (void)hipEventDestroy(b->ev_out);
-    void* ptrs[] = {b->d_psi, b->d_lam, b->d_circ, b->d_pass, b->d_ops, b->d_lays, b->d_segs, b->d_cspec, b->d_cfac, b->d_rtabs, b->d_rmembers, b->d_full, b->d_coef, b->d_coef_f, b->d_epart, b->d_gpart, b->d_e_off, b->d_e_cnt, b->d_g_off, b->d_g_cnt,
-                    b->d_slot_scale, b->d_slot_val, b->d_csr_ptr, b->d_csr_col, b->d_params, b->d_expvals,
-                    b->d_grads};
-    for (void* p : ptrs)
+    for (void* p : {b->d_psi, b->d_lam, b->d_tables})
         if (p) (void)hipFree(p);
     if (b->stream) (void)hipStreamDestroy(b->stream);
     delete b;
 }
 
-hipError_t enqueue_run(sv_batch b)
+// Levels [l0, l1) of a run.
+hipError_t enqueue_levels(sv_batch b, size_t l0, size_t l1, hipStream_t s)
 {
-    hipStream_t s = b->stream;
+    hipError_t e = hipSuccess;
+    for (size_t l = l0; l < l1 && e == hipSuccess; ++l) {
+        const int64_t* lf = &b->level_first[3 * l];
+        e = launch_pass_items(b->tb, b->dtype, PM_FWD, lf[0], lf[1], b->threads, b->lds_fwd, s, b->level_gated[l] != 0);
+        if (e == hipSuccess) e = launch_pass_items(b->tb, b->dtype, PM_OBS, lf[1], lf[2], b->threads, 0, s);
+        if (e == hipSuccess) e = launch_pass_items(b->tb, b->dtype, PM_REV, lf[2], lf[3], b->rthreads, b->lds_rev, s);
+    }
+    return e;
+}
+
+hipError_t enqueue_coef(sv_batch b, hipStream_t s)
+{
     hipError_t e = launch_pass_coef(b->d_cspec, b->n_cspec, b->d_cfac, b->d_params, b->d_coef,
                                     b->dtype == SV_C64 ? b->d_coef_f : nullptr, b->d_full, s);
     if (e == hipSuccess) e = launch_pass_runs(b->d_rtabs, b->n_rtabs, b->d_rmembers, b->d_coef, s);
-    const std::vector<int64_t>& lf = b->level_first;
-    for (size_t l = 0; l + 3 < lf.size() && e == hipSuccess; l += 3) {
-        e = launch_pass_items(b->tb, b->dtype, PM_FWD, lf[l], lf[l + 1], b->threads, b->lds_fwd, s,
-                              b->level_gated[l / 3] != 0);
-        if (e == hipSuccess) e = launch_pass_items(b->tb, b->dtype, PM_OBS, lf[l + 1], lf[l + 2], b->threads, 0, s);
-        if (e == hipSuccess)
-            e = launch_pass_items(b->tb, b->dtype, PM_REV, lf[l + 2], lf[l + 3], b->rthreads, b->lds_rev, s);
-    }
-    if (e == hipSuccess) e = launch_pass_segsum(b->d_epart, b->d_e_off, b->d_e_cnt, nullptr, b->d_expvals, b->n_circ,
-                                               b->d_full, s);
-    if (e == hipSuccess && b->with_grad) {
-        e = launch_pass_segsum(b->d_gpart, b->d_g_off, b->d_g_cnt, b->d_slot_scale, b->d_slot_val, b->n_slots,
-                                                nullptr, s);
-        if (e == hipSuccess) e = launch_pass_grad_csr(b->d_slot_val, b->d_csr_ptr, b->d_csr_col, b->n_params, b->d_grads, s);
-    }
+    return e;
+}
+
+hipError_t enqueue_grad_sums(sv_batch b, hipStream_t s)
+{
+    hipError_t e = launch_pass_segsum(b->d_gpart, b->d_g_off, b->d_g_cnt, b->d_slot_scale, b->d_slot_val, b->n_slots,
+                                      nullptr, s);
+    if (e == hipSuccess) e = launch_pass_grad_csr(b->d_slot_val, b->d_csr_ptr, b->d_csr_col, b->n_params, b->d_grads, s);
+    return e;
+}
+
+hipError_t enqueue_run(sv_batch b)
+{
+    hipStream_t s = b->stream;
+    hipError_t e = enqueue_coef(b, s);
+    if (e == hipSuccess) e = enqueue_levels(b, 0, b->n_levels, s);
+    if (e == hipSuccess)
+        e = launch_pass_segsum(b->d_epart, b->d_e_off, b->d_e_cnt, nullptr, b->d_expvals, b->n_circ, b->d_full, s);
+    if (e == hipSuccess && b->with_grad) e = enqueue_grad_sums(b, s);
     return e;
 }
 
@@ -846,6 +898,11 @@ static sv_status compile_batch(const sv_batch_circuit* circuits, int n_circuits,
     size_t state_total = 0;
     double pass_bytes = 0;
     const size_t eb = dtype == SV_C128 ? 16 : 8;
+    size_t all_ops = 0;
+    for (int c = 0; c < n_circuits; ++c) all_ops += (size_t)std::max(0, circuits[c].n_ops);
+    fops.reserve((with_grad ? 3 : 2) * all_ops);
+    cspec.reserve((with_grad ? 2 : 1) * all_ops + all_ops / 2);
+    cfac.reserve((with_grad ? 2 : 1) * all_ops);
     for (int c = 0; c < n_circuits; ++c) {
         const sv_batch_circuit& bc = circuits[c];
         if (bc.n_qubits < 1 || bc.n_qubits > SV_MAX_QUBITS || bc.n_ops < 0 || (bc.n_ops > 0 && !bc.ops) ||
@@ -1219,8 +1276,7 @@ static DeviceOps device_ops(HostTables& H)
                 return 0;
             };
             uint32_t m = 0;
-            for (int i = 0; i < lanes; ++i)
-                if ((f.cml >> L.pos[i]) & 1u) m |= 1u << i;
+            for (uint32_t c = f.cml; c; c &= c - 1u) m |= 1u << lane_of(__builtin_ctz(c));
             f.cml = m;
             if ((f.kind == FK_DIAG || f.kind == FK_PHASE) && f.ka < 0) f.a = lane_of(f.a);
             if (f.kind == FK_PAIRC && f.kb < 0) f.b = lane_of(f.b);
@@ -1356,15 +1412,23 @@ sv_status sv_batch_plan(const sv_batch_circuit* circuits, int n_circuits, sv_dty
     return SV_OK;
 }
 
-sv_status sv_batch_create(const sv_batch_circuit* circuits, int n_circuits, sv_dtype dtype, const sv_batch_opts* opts,
-                          sv_batch* out)
+// external: the states belong to the caller, who binds them for each run
+// (engine_forward); a run then starts from what psi holds, so nothing is
+// known to be zero.
+static sv_status create_batch(const sv_batch_circuit* circuits, int n_circuits, sv_dtype dtype,
+                              const sv_batch_opts* opts, bool external, sv_batch_s** out)
 {
-    if (!out) return set_error(SV_ERR_ARG, "null output handle");
-    if (dtype != SV_C64 && dtype != SV_C128) return set_error(SV_ERR_ARG, "bad dtype");
     HostTables H;
     {
         sv_status rc = compile_batch(circuits, n_circuits, dtype, opts, H);
         if (rc) return rc;
+    }
+    if (external) {
+        // the gradient partials of all tiles stay within half of a state
+        if ((double)H.g_total * sizeof(double) > 0.5 * (double)H.state_total)
+            return set_error(SV_ERR_UNSUPPORTED, "gradient partials too large");
+        for (FCirc& c : H.circs) c.loaded = 1;
+        for (FPass& p : H.passes) p.support = ~0ull;
     }
     const DeviceOps dops = device_ops(H);
     const int with_grad = H.with_grad, threads = H.threads, n_params = H.n_params, coef_total = dops.coef_total;
@@ -1415,54 +1479,60 @@ sv_status sv_batch_create(const sv_batch_circuit* circuits, int n_circuits, sv_d
         b->nq.push_back(circs[c].n);
         b->max_passes = std::max(b->max_passes, circs[c].n_pass);
     }
-    hipError_t e = hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking);
-    if (e != hipSuccess) {
-        delete b;
-        return hip_fail(e, "stream");
-    }
     b->caller = nullptr;
-    e = hipEventCreateWithFlags(&b->ev_in, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_out, hipEventDisableTiming);
-    if (e != hipSuccess) {
-        batch_release(b);
-        return hip_fail(e, "events");
+    hipError_t e = hipSuccess;
+    if (!external) {
+        e = hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking);
+        if (e != hipSuccess) {
+            delete b;
+            return hip_fail(e, "stream");
+        }
+        e = hipEventCreateWithFlags(&b->ev_in, hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_out, hipEventDisableTiming);
+        if (e != hipSuccess) {
+            batch_release(b);
+            return hip_fail(e, "events");
+        }
+        if (hipMalloc(&b->d_psi, state_total) != hipSuccess ||
+            (with_grad && hipMalloc(&b->d_lam, state_total) != hipSuccess)) {
+            (void)hipGetLastError();
+            batch_release(b);
+            return set_error(SV_ERR_OOM, "batch state allocation failed");
+        }
+        for (int c = 0; c < n_circuits; ++c) {
+            circs[c].psi = (char*)b->d_psi + psi_off[c];
+            circs[c].lam = with_grad ? (char*)b->d_lam + psi_off[c] : nullptr;
+        }
     }
-    if (hipMalloc(&b->d_psi, state_total) != hipSuccess ||
-        (with_grad && hipMalloc(&b->d_lam, state_total) != hipSuccess)) {
-        (void)hipGetLastError();
-        batch_release(b);
-        return set_error(SV_ERR_OOM, "batch state allocation failed");
-    }
-    for (int c = 0; c < n_circuits; ++c) {
-        circs[c].psi = (char*)b->d_psi + psi_off[c];
-        circs[c].lam = with_grad ? (char*)b->d_lam + psi_off[c] : nullptr;
-    }
-    std::vector<double> zeros_e(std::max(1, e_total)), zeros_p(std::max(1, n_params));
-    e = dev_upload(&b->d_circ, circs);
-    if (e == hipSuccess) e = dev_upload(&b->d_pass, passes);
-    if (e == hipSuccess) e = dev_upload(&b->d_ops, dops.ops);
-    if (e == hipSuccess) e = dev_upload(&b->d_rtabs, dops.tabs);
-    if (e == hipSuccess) e = dev_upload(&b->d_rmembers, dops.members);
-    if (e == hipSuccess) e = dev_upload(&b->d_full, std::vector<int32_t>{0});
-    if (e == hipSuccess) e = dev_upload(&b->d_lays, device_layouts(H, dtype == SV_C128 ? 16 : 8));
-    if (e == hipSuccess) e = dev_upload(&b->d_segs, segs);
-    if (e == hipSuccess) e = dev_upload(&b->d_cspec, cspec);
-    if (e == hipSuccess) e = dev_upload(&b->d_cfac, H.cfac);
-    if (e == hipSuccess) e = dev_upload(&b->d_e_off, e_off);
-    if (e == hipSuccess) e = dev_upload(&b->d_e_cnt, e_cnt);
-    if (e == hipSuccess) e = dev_upload(&b->d_g_off, g_off);
-    if (e == hipSuccess) e = dev_upload(&b->d_g_cnt, g_cnt);
-    if (e == hipSuccess) e = dev_upload(&b->d_slot_scale, slot_scale);
-    if (e == hipSuccess) e = dev_upload(&b->d_csr_ptr, csr_ptr);
-    if (e == hipSuccess) e = dev_upload(&b->d_csr_col, csr_col);
-    if (e == hipSuccess) e = hipMalloc((void**)&b->d_coef, sizeof(double) * std::max(1, coef_total));
-    if (e == hipSuccess && dtype == SV_C64) e = hipMalloc((void**)&b->d_coef_f, sizeof(float) * std::max(1, coef_total));
-    if (e == hipSuccess) e = hipMalloc((void**)&b->d_epart, sizeof(double) * std::max(1, e_total));
-    if (e == hipSuccess) e = hipMalloc((void**)&b->d_gpart, sizeof(double) * std::max<int64_t>(1, g_total));
-    if (e == hipSuccess) e = hipMalloc((void**)&b->d_slot_val, sizeof(double) * std::max<size_t>(1, slot_param.size()));
-    if (e == hipSuccess) e = hipMalloc((void**)&b->d_params, sizeof(double) * std::max(1, n_params));
-    if (e == hipSuccess) e = hipMalloc((void**)&b->d_expvals, sizeof(double) * n_circuits);
-    if (e == hipSuccess) e = hipMalloc((void**)&b->d_grads, sizeof(double) * std::max(1, n_params));
+    TableArena A;
+    const std::vector<int32_t> full{0};
+    const std::vector<DLayout> dlays = device_layouts(H, dtype == SV_C128 ? 16 : 8);
+    A.table(&b->d_circ, circs);
+    A.table(&b->d_pass, passes);
+    A.table(&b->d_ops, dops.ops);
+    A.table(&b->d_rtabs, dops.tabs);
+    A.table(&b->d_rmembers, dops.members);
+    A.table(&b->d_full, full);
+    A.table(&b->d_lays, dlays);
+    A.table(&b->d_segs, segs);
+    A.table(&b->d_cspec, cspec);
+    A.table(&b->d_cfac, H.cfac);
+    A.table(&b->d_e_off, e_off);
+    A.table(&b->d_e_cnt, e_cnt);
+    A.table(&b->d_g_off, g_off);
+    A.table(&b->d_g_cnt, g_cnt);
+    A.table(&b->d_slot_scale, slot_scale);
+    A.table(&b->d_csr_ptr, csr_ptr);
+    A.table(&b->d_csr_col, csr_col);
+    A.array(&b->d_coef, coef_total);
+    if (dtype == SV_C64) A.array(&b->d_coef_f, coef_total);
+    A.array(&b->d_epart, e_total);
+    A.array(&b->d_gpart, g_total);
+    A.array(&b->d_slot_val, slot_param.size());
+    A.array(&b->d_params, n_params);
+    A.array(&b->d_expvals, n_circuits);
+    A.array(&b->d_grads, n_params);
+    e = A.place(&b->d_tables);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         batch_release(b);
@@ -1499,9 +1569,55 @@ sv_status sv_batch_create(const sv_batch_circuit* circuits, int n_circuits, sv_d
         batch_release(b);
         return hip_fail(e, "pass engine LDS limit");
     }
+    *out = b;
+    return SV_OK;
+}
+
+sv_status sv_batch_create(const sv_batch_circuit* circuits, int n_circuits, sv_dtype dtype, const sv_batch_opts* opts,
+                          sv_batch* out)
+{
+    if (!out) return set_error(SV_ERR_ARG, "null output handle");
+    if (dtype != SV_C64 && dtype != SV_C128) return set_error(SV_ERR_ARG, "bad dtype");
+    sv_batch_s* b = nullptr;
+    sv_status rc = create_batch(circuits, n_circuits, dtype, opts, false, &b);
+    if (rc) return rc;
     *out = (sv_batch)handle_put(b, HK_BATCH);
     return SV_OK;
 }
+
+namespace svk {
+
+sv_batch_s* engine_create(int n, const sv_op* ops, int n_ops, int n_params, int dtype)
+{
+    const sv_batch_circuit c{n, n_ops, ops, n_params, 1};
+    sv_batch_opts o{};
+    o.with_grad = 1;
+    sv_batch_s* b = nullptr;
+    return create_batch(&c, 1, (sv_dtype)dtype, &o, true, &b) == SV_OK ? b : nullptr;
+}
+
+void engine_free(sv_batch_s* b) { batch_release(b); }
+
+hipError_t engine_forward(sv_batch_s* b, void* psi, void* lam, const double* params, hipStream_t s)
+{
+    hipError_t e = hipSuccess;
+    if (b->n_params > 0)
+        e = hipMemcpyAsync(b->d_params, params, sizeof(double) * b->n_params, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = launch_pass_bind(b->d_circ, psi, lam, s);
+    if (e == hipSuccess) e = enqueue_coef(b, s);
+    if (e == hipSuccess) e = enqueue_levels(b, 0, b->max_passes, s);
+    return e;
+}
+
+hipError_t engine_reverse(sv_batch_s* b, hipStream_t s, const double** grads)
+{
+    hipError_t e = enqueue_levels(b, b->max_passes + 1, b->n_levels, s);  // the observable's level is the caller's
+    if (e == hipSuccess) e = enqueue_grad_sums(b, s);
+    *grads = b->d_grads;
+    return e;
+}
+
+}  // namespace svk
 
 #define SV_BATCH(b)                                                                    \
     sv_batch_s* const b = (sv_batch_s*)handle_get(b##_h, HK_BATCH);                     \

@@ -167,7 +167,7 @@ struct FCirc {
     int32_t cb;            // coalescing bits: every pass's tile holds global bits 0..cb-1 as local bits 0..cb-1
     int32_t reg;           // 1: forward passes are register-tiled (tq >= rb); 0: every op sweeps an LDS tile
     int32_t rreg;          // the same for reverse passes (tq >= reverse rb)
-    int32_t pad_;
+    int32_t loaded;        // 1: a run starts from the state in psi; 0: from |0...0>
     uint64_t all_bits;     // 2^n - 1
 };
 
@@ -246,10 +246,24 @@ hipError_t launch_pass_segsum(const double* part, const int64_t* off, const int*
                               int n_seg, int32_t* clear, hipStream_t s);
 hipError_t launch_pass_grad_csr(const double* slot_val, const int* rowptr, const int* cols, int n_params, double* grad,
                                 hipStream_t s);
+hipError_t launch_pass_bind(FCirc* circ, void* psi, void* lam, hipStream_t s);
 // Dynamic LDS of a pass workgroup: tiles and address map, plus per-slot wave
 // partials for slot_waves waves (reverse passes; 0 for forward ones).
 size_t pass_engine_lds_bytes(int tq_max, int hi_entries, int with_grad, int dtype, int lds_small, int slot_waves);
 // Workgroup size for register width rb: 2^(tq_max - rb), at least one wavefront.
 int pass_engine_threads(int tq_max, int reg_bits);
+
+// The engine on a caller's states (the adjoint sweep of a circuit object):
+// engine_create returns null where the engine does not take the circuit.
+// engine_forward runs every forward pass on psi; the caller then forms lambda
+// = O psi; engine_reverse walks back, leaving psi as it was and the gradient
+// in device memory.  All on stream s; a run at a time per engine.
+}  // namespace svk
+struct sv_batch_s;
+namespace svk {
+sv_batch_s* engine_create(int n, const sv_op* ops, int n_ops, int n_params, int dtype);
+void engine_free(sv_batch_s* b);
+hipError_t engine_forward(sv_batch_s* b, void* psi, void* lam, const double* params, hipStream_t s);
+hipError_t engine_reverse(sv_batch_s* b, hipStream_t s, const double** grads);
 
 }  // namespace svk
