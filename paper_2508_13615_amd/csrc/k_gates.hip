@@ -79,6 +79,170 @@ __device__ __forceinline__ void pair_apply(const V a0, const V a1, const Coef2<T
     }
 }
 
+// The 2x2 updates of k_small_circuit, with the products rounded in the order
+// the single-gate kernels round them, so that a complex64 circuit ends in the
+// same amplitudes either way.
+__device__ __forceinline__ double small_fma(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float small_fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+template <typename V, typename T>
+__device__ __forceinline__ V small_mul(T ur, T ui, V a)
+{
+    V r;
+    r.x = small_fma(ur, a.x, -(ui * a.y));
+    r.y = small_fma(ui, a.x, ur * a.y);
+    return r;
+}
+
+template <typename V, typename T>
+__device__ __forceinline__ V small_mad2(T ur, T ui, V a, T wr, T wi, V b)
+{
+    const V p = small_mul(ur, ui, a), q = small_mul(wr, wi, b);
+    V r;
+    r.x = p.x + q.x;
+    r.y = p.y + q.y;
+    return r;
+}
+
+template <typename V, typename T>
+__device__ __forceinline__ void small_rx(T c, T m, V a, V b, V& r, V& q)  // m = -sin
+{
+    r.x = small_fma(c, a.x, -(m * b.y));
+    q.x = small_fma(c, b.x, -(m * a.y));
+    r.y = small_fma(c, a.y, m * b.x);
+    q.y = small_fma(m, a.x, c * b.y);
+}
+
+// A circuit on a state that fits a workgroup's LDS (SmallProgram): the state
+// is read and written once and a gate costs an LDS sweep and a barrier, 1.3 us
+// at 13 qubits complex64, where a launch per gate costs 3.7 us however small
+// the state is (65 gates and the Ising energy: 300 -> 131 us).  What bounds
+// it: vector issue on the one CU (about 30 instructions a pair); grouping
+// gates by target to sweep the LDS less often cost more instructions and
+// measured slower (59 against 43 us for half of those gates).  Larger states,
+// which fill the chip gate by gate, do not come here.
+template <typename T>
+__global__ void __launch_bounds__(kSmallThreads)
+k_small_circuit(typename Vec2<T>::type* __restrict__ psi, int n, SmallProgram prog)
+{
+    using V = typename Vec2<T>::type;
+    extern __shared__ double small_lds[];
+    V* const A = (V*)small_lds;
+    const uint32_t na = 1u << n, tid = threadIdx.x;
+    for (uint32_t i = tid; i < na; i += kSmallThreads) A[i] = psi[i];
+    __syncthreads();
+    for (int k = 0; k < prog.n_ops; ++k) {
+        const SmallOp& op = prog.op[k];
+        const uint32_t cm = op.cm, tb = 1u << op.t;
+        Coef2<T> c;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) c.m[i] = (T)op.m[i];
+        auto pairs = [&](auto apply) {
+            for (uint32_t p = tid; p < na / 2; p += kSmallThreads) {
+                const uint32_t i0 = ((p >> op.t) << (op.t + 1)) | (p & (tb - 1u));
+                if ((i0 & cm) != cm) continue;
+                V r0, r1;
+                apply(A[i0], A[i0 | tb], r0, r1);
+                A[i0] = r0;
+                A[i0 | tb] = r1;
+            }
+        };
+        auto ones = [&](auto apply) {  // cm holds the target
+            for (uint32_t i = tid; i < na; i += kSmallThreads)
+                if ((i & cm) == cm) A[i] = apply(A[i]);
+        };
+        switch (op.kind) {
+        case PAIR_SWAP: pairs([&](V a, V b, V& r, V& q) { pair_apply<PAIR_SWAP, T, V>(a, b, c, r, q); }); break;
+        case PAIR_Y: pairs([&](V a, V b, V& r, V& q) { pair_apply<PAIR_Y, T, V>(a, b, c, r, q); }); break;
+        case PAIR_REAL: pairs([&](V a, V b, V& r, V& q) { pair_apply<PAIR_REAL, T, V>(a, b, c, r, q); }); break;
+        case PAIR_RX: pairs([&](V a, V b, V& r, V& q) { small_rx(c.m[0], c.m[3], a, b, r, q); }); break;
+        case PAIR_DENSE:
+            pairs([&](V a, V b, V& r, V& q) {
+                r = small_mad2(c.m[0], c.m[1], a, c.m[2], c.m[3], b);
+                q = small_mad2(c.m[4], c.m[5], a, c.m[6], c.m[7], b);
+            });
+            break;
+        case PAIR_DIAG:
+            pairs([&](V a, V b, V& r, V& q) {
+                r = small_mul(c.m[0], c.m[1], a);
+                q = small_mul(c.m[6], c.m[7], b);
+            });
+            break;
+        case kSmallOne + ONE_NEG:
+            ones([&](V a) {
+                V r;
+                r.x = -a.x;
+                r.y = -a.y;
+                return r;
+            });
+            break;
+        case kSmallOne + ONE_MULI:
+            ones([&](V a) {
+                V r;
+                r.x = c.m[0] > T(0) ? -a.y : a.y;
+                r.y = c.m[0] > T(0) ? a.x : -a.x;
+                return r;
+            });
+            break;
+        case kSmallOne + ONE_MUL: ones([&](V a) { return small_mul(c.m[0], c.m[1], a); }); break;
+        default: {  // two targets
+            const uint32_t ub = 1u << op.u;
+            const int lo = op.t < op.u ? op.t : op.u, hi = op.t < op.u ? op.u : op.t;
+            for (uint32_t p = tid; p < na / 4; p += kSmallThreads) {
+                uint32_t i = ((p >> lo) << (lo + 1)) | (p & ((1u << lo) - 1u));
+                i = ((i >> hi) << (hi + 1)) | (i & ((1u << hi) - 1u));
+                if ((i & cm) != cm) continue;
+                if (op.kind == kSmallSwap) {
+                    const V a = A[i | tb];
+                    A[i | tb] = A[i | ub];
+                    A[i | ub] = a;
+                    continue;
+                }
+                const uint32_t at[4] = {i, i | ub, i | tb, i | tb | ub};
+                V v[4], r[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[j] = A[at[j]];
+#pragma unroll
+                for (int row = 0; row < 4; ++row) {
+                    const SmallOp& cr = prog.op[k + row];
+                    T sr = T(0), si = T(0);
+#pragma unroll
+                    for (int col = 0; col < 4; ++col) {
+                        const T ur = (T)cr.m[2 * col], ui = (T)cr.m[2 * col + 1];
+                        sr += ur * v[col].x - ui * v[col].y;
+                        si += ur * v[col].y + ui * v[col].x;
+                    }
+                    r[row].x = sr;
+                    r[row].y = si;
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) A[at[j]] = r[j];
+            }
+            if (op.kind == kSmallQuad) k += 3;
+            break;
+        }
+        }
+        __syncthreads();
+    }
+    for (uint32_t i = tid; i < na; i += kSmallThreads) psi[i] = A[i];
+}
+
+template <typename T>
+hipError_t launch_small_circuit(void* psi, int n, const SmallProgram& p, hipStream_t s)
+{
+    using V = typename Vec2<T>::type;
+    const size_t bytes = ((size_t)1 << n) * sizeof(V);
+    if (bytes > kSmallStateBytes || p.n_ops < 1 || p.n_ops > kSmallOps) return hipErrorInvalidValue;
+    // the limit is only ever set to the one value
+    hipError_t e = hipFuncSetAttribute((const void*)k_small_circuit<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)kSmallStateBytes);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_small_circuit<T>), dim3(1), dim3(kSmallThreads), bytes, s, (V*)psi, n, p);
+    return hipGetLastError();
+}
+template hipError_t launch_small_circuit<double>(void*, int, const SmallProgram&, hipStream_t);
+template hipError_t launch_small_circuit<float>(void*, int, const SmallProgram&, hipStream_t);
+
 template <typename T, int OP, int U, bool NT>
 __global__ void __launch_bounds__(1024)
 k_pair(typename Vec2<T>::type* __restrict__ psi, GroupSpec gs, uint64_t o0, uint64_t o1, Coef2<T> c)

@@ -1516,6 +1516,58 @@ static sv_status circuit_forward(sv_circuit c, sv_state st, const double* params
     return SV_OK;
 }
 
+// ---- circuits on small states -----------------------------------------------
+
+// Whether a circuit's gates run in one workgroup (k_small_circuit): the state
+// fits its LDS, and there is more than one gate to share the round trip.
+static bool small_circuit(const sv_circuit_s* c, const sv_state_s* st)
+{
+    return c->ops.size() > 1 && (elem_bytes(st->dtype) << st->n) <= kSmallStateBytes;
+}
+
+static sv_status circuit_forward_small(sv_circuit c, sv_state st, const double* params)
+{
+    SmallProgram prog;
+    prog.n_ops = prog.pad = 0;
+    auto flush = [&]() {
+        if (!prog.n_ops) return SV_OK;
+        const hipError_t e = st->dtype == SV_C128 ? launch_small_circuit<double>(st->data, st->n, prog, st->stream)
+                                                  : launch_small_circuit<float>(st->data, st->n, prog, st->stream);
+        prog.n_ops = 0;
+        return hip_status(e, "small circuit launch");
+    };
+    for (const OpRec& o : c->ops) {
+        Plan pl;
+        sv_status rc = op_plan(c, st->dtype, o, params, 0, &pl);
+        if (rc) return rc;
+        if (pl.kind == PK_NOP) continue;
+        const int entries = o.gate == SV_U4 ? 4 : 1;
+        if (prog.n_ops + entries > kSmallOps) {
+            rc = flush();
+            if (rc) return rc;
+        }
+        SmallOp* so = &prog.op[prog.n_ops];
+        memset(so, 0, sizeof(SmallOp) * entries);
+        for (int j = 0; j < o.nc; ++j) so->cm |= 1u << o.q[j];
+        so->t = (uint8_t)o.q[o.nc];
+        if (o.gate == SV_U4 || o.gate == SV_SWAP) {
+            so->kind = o.gate == SV_U4 ? kSmallQuad : kSmallSwap;
+            so->u = (uint8_t)o.q[o.nc + 1];
+            if (o.gate == SV_U4)
+                for (int e = 0; e < 4; ++e) memcpy(so[e].m, o.matrix.data() + 8 * e, sizeof so->m);
+        } else if (pl.kind == PK_ONE) {
+            so->kind = (uint8_t)(kSmallOne + pl.op);
+            so->cm |= 1u << so->t;
+            memcpy(so->m, pl.m, 2 * sizeof(double));
+        } else {
+            so->kind = (uint8_t)pl.op;
+            memcpy(so->m, pl.m, sizeof so->m);
+        }
+        prog.n_ops += entries;
+    }
+    return flush();
+}
+
 // ---- runs of diagonal gates -------------------------------------------------
 
 // Phase terms (mask, angle in half-turns) of a diagonal op: exp(i pi turns)
@@ -1740,6 +1792,7 @@ sv_status sv_circuit_apply_fused(sv_circuit c_h, sv_state st_h, const double* pa
     SV_STATE(st);
     if (st->n != c->n) return set_error(SV_ERR_ARG, "state size does not match the circuit");
     if (c->n_params > 0 && !params) return set_error(SV_ERR_ARG, "null params");
+    if (small_circuit(c, st)) return circuit_forward_small(c, st, params);
     return circuit_forward_fused(c, st, params);
 }
 
@@ -1976,6 +2029,7 @@ sv_status sv_circuit_apply(sv_circuit c_h, sv_state st_h, const double* params)
     SV_STATE(st);
     if (st->n != c->n) return set_error(SV_ERR_ARG, "state size does not match the circuit");
     if (c->n_params > 0 && !params) return set_error(SV_ERR_ARG, "null params");
+    if (small_circuit(c, st)) return circuit_forward_small(c, st, params);
     return circuit_forward(c, st, params);
 }
 

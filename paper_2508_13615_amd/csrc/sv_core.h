@@ -199,6 +199,32 @@ hipError_t launch_quad(void* psi, const GroupSpec& gs, const uint64_t off[4], co
 template <typename T>
 hipError_t launch_general(void* psi, const GroupSpec& gs, int k, const uint64_t* off, const T* m,
                           hipStream_t s, Launch lc);
+// A run of gates on a small state: one workgroup keeps the whole state in
+// LDS and applies the gates in turn (k_small_circuit).  The gates travel in
+// the kernel arguments.
+constexpr size_t kSmallStateBytes = 128 << 10;  // of a CU's 160 KiB
+constexpr int kSmallThreads = 1024;
+enum SmallKind : int {  // PairOp values below kSmallOne, then OneOp values, then two-target gates
+    kSmallOne = 8,
+    kSmallSwap = 16,
+    kSmallQuad = 17  // 4x4: the coefficients run on through the next 3 entries
+};
+struct SmallOp {
+    uint32_t cm;       // bits that must all be 1
+    uint8_t kind;
+    uint8_t t, u;      // target bits (matrix: t is the most significant)
+    uint8_t pad;
+    double m[8];
+};
+constexpr int kSmallOps = 48;
+struct SmallProgram {
+    int32_t n_ops;  // entries
+    int32_t pad;
+    SmallOp op[kSmallOps];
+};
+static_assert(sizeof(SmallProgram) <= 3600, "travels in the kernel arguments");
+template <typename T>
+hipError_t launch_small_circuit(void* psi, int n, const SmallProgram& p, hipStream_t s);
 template <typename T>
 hipError_t launch_set_basis(void* psi, uint64_t n_amps, uint64_t index, hipStream_t s);
 
