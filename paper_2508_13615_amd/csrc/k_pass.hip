@@ -1111,6 +1111,7 @@ __device__ __forceinline__ void item_reg_fwd(const PassTables& tb, const FCirc& 
     const bool sparse = *as_const(tb.full) == 0;
     const uint64_t outside = sparse ? ~pp->support : 0ull;
     if (tile_base & outside) {
+        if (tb.fuse_obs && pidx == cc.n_pass - 1 && threadIdx.x == 0) tb.e_part[cc.e_part_begin + tile] = 0.0;
         if (pidx == cc.n_pass - 1 && active) {
             const uint64_t lane = lane_global(lays + cur, tl);
             V z;
@@ -1252,10 +1253,26 @@ __device__ __forceinline__ void item_reg_fwd(const PassTables& tb, const FCirc& 
             __syncthreads();
         }
     }
+    const uint64_t lane = lane_global(lays + cur, tl);
     if (active) {
-        const uint64_t lane = lane_global(lays + cur, tl);
 #pragma unroll
         for (int j = 0; j < R; ++j) stg<true>((V*)(psi + lays[cur].reg_g[j] + lane), v[j]);
+    }
+    // A forward-only run takes <psi|O|psi> here, from the registers, instead of
+    // reading the state once more (item_observable).
+    if (tb.fuse_obs && pidx == cc.n_pass - 1) {
+        const uint64_t x0 = (tile_base * sizeof(V) + lane) / sizeof(V);
+        const uint64_t zzmask = cc.all_bits >> 1;
+        double acc = 0.0;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const uint64_t x = x0 | lays[cur].reg_g[j] / sizeof(V);
+            const int o = cc.obs_kind == 1 ? cc.n - 2 * (int)__popcll(x)
+                                           : (cc.n - 1) - 2 * (int)__popcll((x ^ (x >> 1)) & zzmask);
+            acc += (double)o * ((double)v[j].x * (double)v[j].x + (double)v[j].y * (double)v[j].y);
+        }
+        const double s = block_sum_fixed(active ? acc : 0.0, (double*)lds);
+        if (threadIdx.x == 0) tb.e_part[cc.e_part_begin + tile] = s;
     }
 }
 
@@ -1774,17 +1791,26 @@ __global__ void k_pass_bind(FCirc* circ, void* psi, void* lam)
     circ->lam = lam;
 }
 
-// out[k] = scale[k] * sum_{i < cnt[k]} part[off[k] + i], fixed order.
-__global__ void __launch_bounds__(256)
+// out[k] = scale[k] * sum_{i < cnt[k]} part[off[k] + i], fixed order.  Eight
+// independent loads a thread.
+constexpr int kSegsumThreads = 512;
+__global__ void __launch_bounds__(kSegsumThreads)
 k_pass_segsum(const double* __restrict__ part, const int64_t* __restrict__ off, const int* __restrict__ cnt,
               const double* __restrict__ scale, double* __restrict__ out, int32_t* __restrict__ clear)
 {
-    __shared__ double red[4];
+    __shared__ double red[kSegsumThreads / 64];
     if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
-    const int k = blockIdx.x;
+    const int k = blockIdx.x, n = cnt[k];
     const double* p = part + off[k];
-    double acc = 0.0;
-    for (int i = threadIdx.x; i < cnt[k]; i += blockDim.x) acc += p[i];
+    double a[8] = {};
+    for (int i = threadIdx.x; i < n; i += 8 * kSegsumThreads) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int x = i + j * kSegsumThreads;
+            if (x < n) a[j] += p[x];
+        }
+    }
+    double acc = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
     acc = wave_sum(acc);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
@@ -1903,7 +1929,7 @@ hipError_t launch_pass_segsum(const double* part, const int64_t* off, const int*
                               int n_seg, int32_t* clear, hipStream_t s)
 {
     if (n_seg <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pass_segsum, dim3(n_seg), dim3(256), 0, s, part, off, cnt, scale, out, clear);
+    hipLaunchKernelGGL(k_pass_segsum, dim3(n_seg), dim3(kSegsumThreads), 0, s, part, off, cnt, scale, out, clear);
     return hipGetLastError();
 }
 

@@ -559,6 +559,11 @@ struct sv_batch_s {
     double* d_gpart;
     int64_t* d_e_off;
     int* d_e_cnt;
+    // chunks of long energy sums, summed first (n_echunks 0: none)
+    int64_t* d_ec_off;
+    int* d_ec_cnt;
+    double* d_echunk;
+    int n_echunks;
     int64_t* d_g_off;
     int* d_g_cnt;
     double* d_slot_scale;
@@ -649,7 +654,8 @@ hipError_t enqueue_levels(sv_batch b, size_t l0, size_t l1, hipStream_t s)
     for (size_t l = l0; l < l1 && e == hipSuccess; ++l) {
         const int64_t* lf = &b->level_first[3 * l];
         e = launch_pass_items(b->tb, b->dtype, PM_FWD, lf[0], lf[1], b->threads, b->lds_fwd, s, b->level_gated[l] != 0);
-        if (e == hipSuccess) e = launch_pass_items(b->tb, b->dtype, PM_OBS, lf[1], lf[2], b->threads, 0, s);
+        if (e == hipSuccess && !b->tb.fuse_obs)
+            e = launch_pass_items(b->tb, b->dtype, PM_OBS, lf[1], lf[2], b->threads, 0, s);
         if (e == hipSuccess) e = launch_pass_items(b->tb, b->dtype, PM_REV, lf[2], lf[3], b->rthreads, b->lds_rev, s);
     }
     return e;
@@ -676,8 +682,11 @@ hipError_t enqueue_run(sv_batch b)
     hipStream_t s = b->stream;
     hipError_t e = enqueue_coef(b, s);
     if (e == hipSuccess) e = enqueue_levels(b, 0, b->n_levels, s);
+    if (e == hipSuccess && b->n_echunks)
+        e = launch_pass_segsum(b->d_epart, b->d_ec_off, b->d_ec_cnt, nullptr, b->d_echunk, b->n_echunks, nullptr, s);
     if (e == hipSuccess)
-        e = launch_pass_segsum(b->d_epart, b->d_e_off, b->d_e_cnt, nullptr, b->d_expvals, b->n_circ, b->d_full, s);
+        e = launch_pass_segsum(b->n_echunks ? b->d_echunk : b->d_epart, b->d_e_off, b->d_e_cnt, nullptr, b->d_expvals,
+                               b->n_circ, b->d_full, s);
     if (e == hipSuccess && b->with_grad) e = enqueue_grad_sums(b, s);
     return e;
 }
@@ -1504,6 +1513,22 @@ static sv_status create_batch(const sv_batch_circuit* circuits, int n_circuits, 
             circs[c].lam = with_grad ? (char*)b->d_lam + psi_off[c] : nullptr;
         }
     }
+    // One workgroup reads 2^19 partials in 280 us; in chunks it is a few.
+    constexpr int kChunk = 4096;
+    std::vector<int64_t> ec_off;
+    std::vector<int> ec_cnt;
+    if (*std::max_element(e_cnt.begin(), e_cnt.end()) > 2 * kChunk)
+        for (int c = 0; c < n_circuits; ++c) {
+            const int64_t off = e_off[c];
+            const int cnt = e_cnt[c], first = (int)ec_off.size();
+            for (int i = 0; i < cnt; i += kChunk) {
+                ec_off.push_back(off + i);
+                ec_cnt.push_back(std::min(kChunk, cnt - i));
+            }
+            e_off[c] = first;
+            e_cnt[c] = (int)ec_off.size() - first;
+        }
+    b->n_echunks = (int)ec_off.size();
     TableArena A;
     const std::vector<int32_t> full{0};
     const std::vector<DLayout> dlays = device_layouts(H, dtype == SV_C128 ? 16 : 8);
@@ -1519,6 +1544,8 @@ static sv_status create_batch(const sv_batch_circuit* circuits, int n_circuits, 
     A.table(&b->d_cfac, H.cfac);
     A.table(&b->d_e_off, e_off);
     A.table(&b->d_e_cnt, e_cnt);
+    A.table(&b->d_ec_off, ec_off);
+    A.table(&b->d_ec_cnt, ec_cnt);
     A.table(&b->d_g_off, g_off);
     A.table(&b->d_g_cnt, g_cnt);
     A.table(&b->d_slot_scale, slot_scale);
@@ -1527,6 +1554,7 @@ static sv_status create_batch(const sv_batch_circuit* circuits, int n_circuits, 
     A.array(&b->d_coef, coef_total);
     if (dtype == SV_C64) A.array(&b->d_coef_f, coef_total);
     A.array(&b->d_epart, e_total);
+    A.array(&b->d_echunk, ec_off.size());
     A.array(&b->d_gpart, g_total);
     A.array(&b->d_slot_val, slot_param.size());
     A.array(&b->d_params, n_params);
@@ -1557,6 +1585,8 @@ static sv_status create_batch(const sv_batch_circuit* circuits, int n_circuits, 
     tb.reg_bits = H.reg_bits;
     tb.rreg_bits = H.rreg_bits;
     tb.lds_small = H.lds_small;
+    // a forward-only run whose circuits are all register-tiled takes the observable in its last passes
+    tb.fuse_obs = !with_grad && !H.lds_small;
     // the forward exchange needs half a tile unless some op or circuit works on a tile in LDS
     tb.lds_half = dtype == SV_C128 && !H.lds_small;
     for (const FPass& fp : passes)

@@ -225,6 +225,7 @@ struct PassTables {
     int32_t hi_entries;  // LDS address-map entries: max over circuits of 2^(tq - cb)
     int32_t reg_bits;    // rb of register-tiled forward passes
     int32_t rreg_bits;   // rb of register-tiled reverse passes
+    int32_t fuse_obs;    // 1: the last forward pass takes the observable's partials (no separate stage)
     int32_t lds_half;    // 1: complex128 forward passes exchange through half a tile of LDS
     int32_t lds_small;   // 1 if some circuit takes the LDS-sweep form (tq < rb)
 };
