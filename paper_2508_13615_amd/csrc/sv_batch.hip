@@ -1396,13 +1396,49 @@ sv_status sv_tune_engine_get(int dtype, int with_grad, int* tile_qubits, int* am
     return SV_OK;
 }
 
+// A batch's plan.  A forward-only complex128 run of one large circuit may take
+// a larger tile than the tuned one where that saves passes: its passes are
+// bound by HBM when they hold few ops each, so the tile of 10 to 12 qubits
+// with the fewest passes wins (ties: the smaller).  Measured at 16 amplitudes
+// per thread, tiles of 10 / 11 / 12: 29-qubit HEA (13 ops a pass) 91.3 / 80.8 /
+// 82.3 ms, 26-qubit HEA 9.98 / 6.92 / 7.62, 24-qubit HEA 1.54 / 1.67 / 1.40;
+// but the 28-qubit universal circuit (60 ops a pass, bound by instruction
+// issue) 31.4 / 32.8 / 34.5 and 26 qubits of mixed gates, whose 4x4 gates
+// sweep the tile in LDS, 6.41 / 6.93 / 6.86: those keep the tuned tile.  So do
+// states below 24 qubits, which the 256 MiB last-level cache holds: 21-qubit
+// HEA 0.423 / 0.410 / 0.417, 22-qubit QFT 0.205 / 0.210 / 0.225.
+static sv_status plan_batch(const sv_batch_circuit* circuits, int n_circuits, int dtype, const sv_batch_opts* opts,
+                            HostTables& H)
+{
+    constexpr int kMinQubits = 24, kMaxOpsPerPass = 24, kTile = 10, kMaxTile = 12;
+    sv_status rc = compile_batch(circuits, n_circuits, dtype, opts, H);
+    if (rc || n_circuits != 1 || dtype != SV_C128 || H.with_grad || (opts && opts->tile_qubits > 0) ||
+        H.tq_max != kTile || H.reg_bits != 4 || circuits[0].n_qubits < kMinQubits)
+        return rc;
+    int ops = 0;  // a run of phases counts once
+    for (const FOp& f : H.fops) {
+        if (f.kind == FK_QUAD) return rc;
+        ops += f.kind != FK_LAYOUT && !(f.kind == FK_PHASE && (f.kb == 1 || f.kb == 2));
+    }
+    if (ops > kMaxOpsPerPass * (int)H.passes.size()) return rc;
+    sv_batch_opts o{};
+    if (opts) o = *opts;
+    for (int tq = kTile + 1; tq <= kMaxTile; ++tq) {
+        o.tile_qubits = tq;
+        HostTables X;
+        if (compile_batch(circuits, n_circuits, dtype, &o, X) == SV_OK && X.passes.size() < H.passes.size())
+            H = std::move(X);
+    }
+    return SV_OK;
+}
+
 sv_status sv_batch_plan(const sv_batch_circuit* circuits, int n_circuits, sv_dtype dtype, const sv_batch_opts* opts,
                         int64_t* info)
 {
     if (!info) return set_error(SV_ERR_ARG, "null info");
     if (dtype != SV_C64 && dtype != SV_C128) return set_error(SV_ERR_ARG, "bad dtype");
     HostTables H;
-    sv_status rc = compile_batch(circuits, n_circuits, dtype, opts, H);
+    sv_status rc = plan_batch(circuits, n_circuits, dtype, opts, H);
     if (rc) return rc;
     int maxp = 0;
     for (const FCirc& c : H.circs) maxp = std::max(maxp, c.n_pass);
@@ -1429,7 +1465,7 @@ static sv_status create_batch(const sv_batch_circuit* circuits, int n_circuits, 
 {
     HostTables H;
     {
-        sv_status rc = compile_batch(circuits, n_circuits, dtype, opts, H);
+        sv_status rc = plan_batch(circuits, n_circuits, dtype, opts, H);
         if (rc) return rc;
     }
     if (external) {
