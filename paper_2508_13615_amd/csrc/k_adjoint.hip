@@ -172,6 +172,108 @@ k_obs_pauli_apply(const typename Vec2<T>::type* __restrict__ psi, typename Vec2<
     }
 }
 
+// lam (=|+=) the terms of one ObsTilePass applied to psi.  A workgroup holds one
+// tile of psi in LDS; a thread forms lambda for its eight amplitudes: the
+// diagonal terms give one factor per amplitude (per register part of the zmasks
+// a signed sum of coefficients, then a Walsh-Hadamard transform over the
+// register bits), an off-diagonal term one LDS read, one sign and two
+// multiply-adds, and terms on one xmask share the read.  lambda is written once
+// a pass instead of read and written once a term.  21 qubits complex128,
+// transverse-field Ising (20 ZZ and 21 X): two launches of 27 us against 22 of
+// 15, and the whole energy and gradient 1.24 -> 0.97 ms.  What bounds it: the
+// last-level cache (64 MiB of amplitudes read and written per launch).
+__global__ void __launch_bounds__(kObsTileThreads)
+k_obs_tile_apply(const double2* __restrict__ psi, double2* __restrict__ lam, ObsTilePass ps, int accumulate)
+{
+    constexpr int R = 1 << kObsRegBits;
+    constexpr int kLaneBits = kObsTileBits - kObsRegBits;
+    __shared__ double2 lds[1 << kObsTileBits];
+    const uint32_t t = threadIdx.x, na = 1u << ps.tq;
+    uint64_t base = blockIdx.x, toff = 0;
+    for (int k = 0; k < ps.tq; ++k) {
+        const int p = ps.q[k];
+        base = ((base >> p) << (p + 1)) | (base & ((1ull << p) - 1ull));
+    }
+#pragma unroll
+    for (int i = 0; i < kLaneBits; ++i)
+        if (i < ps.tq) toff |= (uint64_t)((t >> i) & 1u) << ps.q[i];
+    uint64_t roff[R];
+    roff[0] = 0;
+#pragma unroll
+    for (int j = 1; j < R; ++j) {
+        const int b = __builtin_ctz(j);
+        roff[j] = roff[j & (j - 1)] | (kLaneBits + b < ps.tq ? 1ull << ps.q[kLaneBits + b] : 0ull);
+    }
+    double2 a[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const uint32_t l = t + (uint32_t)j * kObsTileThreads;
+        a[j].x = a[j].y = 0.0;
+        if (l < na) lds[l] = a[j] = psi[base | toff | roff[j]];
+    }
+    double o[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        o[j] = 0.0;
+        for (int k = ps.dstart[j]; k < ps.dstart[j + 1]; ++k) {
+            const ObsDiagTerm d = ps.diag[k];
+            o[j] += flip_if(d.c, (uint32_t)__popcll(base & d.z) + (uint32_t)__popc(t & d.zl));
+        }
+    }
+#pragma unroll
+    for (int h = 1; h < R; h <<= 1)
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+            if (!(j & h)) {
+                const double u = o[j], v = o[j | h];
+                o[j] = u + v;
+                o[j | h] = u - v;
+            }
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        a[j].x *= o[j];
+        a[j].y *= o[j];
+    }
+    __syncthreads();
+    double2 b[R];
+    ObsOffTerm nx = ps.off[0];
+    for (int k = 0; k < ps.n_off; ++k) {
+        const ObsOffTerm m = nx;
+        nx = ps.off[k + 1 < kObsTileOff ? k + 1 : k];
+        if (m.first) {
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const uint32_t l = t + (uint32_t)j * kObsTileThreads;
+                b[j].x = b[j].y = 0.0;
+                if (l < na) b[j] = lds[l ^ m.f];
+            }
+        }
+        const double c = flip_if(0.5 * m.c, (uint32_t)__popcll(base & m.z));
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const double s = flip_if(c, (uint32_t)__popc(((t + (uint32_t)j * kObsTileThreads) ^ m.f) & m.zl));
+            if (m.imag) {  // -i
+                a[j].x += s * b[j].y;
+                a[j].y -= s * b[j].x;
+            } else {
+                a[j].x += s * b[j].x;
+                a[j].y += s * b[j].y;
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        if (t + (uint32_t)j * kObsTileThreads >= na) continue;
+        double2* const p = lam + (base | toff | roff[j]);
+        if (accumulate) {
+            const double2 l = *p;
+            a[j].x += l.x;
+            a[j].y += l.y;
+        }
+        *p = a[j];
+    }
+}
+
 template <typename T>
 __global__ void __launch_bounds__(kReduceThreads)
 k_inner_partial(const typename Vec2<T>::type* __restrict__ a, const typename Vec2<T>::type* __restrict__ b,
@@ -264,6 +366,16 @@ hipError_t launch_obs_pauli_apply(const void* psi, void* lam, int n, uint64_t xm
     const uint64_t na = 1ull << n;
     hipLaunchKernelGGL((k_obs_pauli_apply<T>), dim3(elementwise_grid(na)), dim3(256), 0, s, (const V*)psi, (V*)lam,
                        na, xmask, zmask, ny, coeff);
+    return hipGetLastError();
+}
+
+hipError_t launch_obs_tile_apply(const void* psi, void* lam, int n, const ObsTilePass& ps, int accumulate,
+                                 hipStream_t s)
+{
+    const uint64_t tiles = 1ull << (n - ps.tq);
+    if (ps.tq != std::min(n, kObsTileBits) || tiles >= (1ull << 31)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_obs_tile_apply, dim3((uint32_t)tiles), dim3(kObsTileThreads), 0, s, (const double2*)psi,
+                       (double2*)lam, ps, accumulate);
     return hipGetLastError();
 }
 

@@ -156,12 +156,6 @@ k_diag_obs_partial(const typename Vec2<T>::type* __restrict__ psi, uint64_t n_am
     if (threadIdx.x == 0) partials[blockIdx.x] = coeff * s;
 }
 
-// v with its sign flipped where the lowest bit of `odd` is set.
-__device__ __forceinline__ double flip_if(double v, uint32_t odd)
-{
-    return __hiloint2double(__double2hiint(v) ^ (int)(odd << 31), __double2loint(v));
-}
-
 // Many Pauli terms in one read of the state (ObsTilePass).  A term's xmask
 // lies inside the tile, so both amplitudes of each of its pairs are in the
 // workgroup's LDS copy; its zmask's bits outside the tile are one sign per

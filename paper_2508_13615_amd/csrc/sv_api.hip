@@ -1148,6 +1148,25 @@ static void obs_tile_fill(int n, const P& op, size_t d0, size_t d1, ObsTileBuild
     ps.dstart[1 << kObsRegBits] = (uint8_t)nd;
 }
 
+// The next pass's terms: from off-diagonal term k on those not done that fit
+// a tile together with the qubits `low`, and the next diagonal terms from d0.
+template <typename P, typename Done>
+static void obs_tile_take(int n, const P& op, Done& done, size_t k, uint64_t low, size_t& d0, ObsTileBuild& b)
+{
+    const int tq = std::min(n, kObsTileBits);
+    b.Q = low;
+    b.n_off = 0;
+    for (size_t j = k; j < op.oc.size() && b.n_off < kObsTileOff; ++j) {
+        if (done[j] || __builtin_popcountll(b.Q | op.ox[j]) > tq) continue;
+        done[j] = 1;
+        b.Q |= op.ox[j];
+        b.term[b.n_off++] = (int)j;
+    }
+    const size_t d1 = std::min(op.dc.size(), d0 + kObsTileDiag);
+    obs_tile_fill(n, op, d0, d1, b);
+    d0 = d1;
+}
+
 // Whether an off-diagonal term fits a k_obs_tile pass: its xmask and the
 // coalescing bits (whole 128-byte lines) within the tile.
 static uint64_t obs_tile_low(int n, int dtype)
@@ -1189,27 +1208,13 @@ static hipError_t obs_passes_in(sv_state st, const P& op, Done& done, double* pa
             continue;
         }
         ObsTileBuild b;
-        b.Q = low;
-        b.n_off = 0;
-        for (size_t j = k; j < n_off && b.n_off < kObsTileOff; ++j) {
-            if (done[j] || __builtin_popcountll(b.Q | op.ox[j]) > tq) continue;
-            done[j] = 1;
-            b.Q |= op.ox[j];
-            b.term[b.n_off++] = (int)j;
-        }
-        const size_t d1 = std::min(n_diag, d0 + kObsTileDiag);
-        obs_tile_fill(n, op, d0, d1, b);
-        d0 = d1;
+        obs_tile_take(n, op, done, k, low, d0, b);
         e = launch_obs_tile<T>(st->data, n, b.ps, partials + off, st->stream);
         off += obs_tile_blocks(n);
     }
     while (d0 < n_diag && e == hipSuccess) {
         ObsTileBuild b;
-        b.Q = 0;
-        b.n_off = 0;
-        const size_t d1 = std::min(n_diag, d0 + kObsTileDiag);
-        obs_tile_fill(n, op, d0, d1, b);
-        d0 = d1;
+        obs_tile_take(n, op, done, n_off, 0, d0, b);
         e = launch_obs_tile<T>(st->data, n, b.ps, partials + off, st->stream);
         off += obs_tile_blocks(n);
     }
@@ -2033,9 +2038,49 @@ sv_status sv_circuit_apply(sv_circuit c_h, sv_state st_h, const double* params)
     return circuit_forward(c, st, params);
 }
 
+// lam = O psi, complex128: the terms that fit tiles in one pass per tile choice
+// (k_obs_tile_apply), a term whose xmask is too wide by itself.  A closed-form
+// diagonal alone keeps its one-pass kernel.  complex64 stays term by term:
+// there lambda is rounded to float after each term, and an energy and gradient
+// returned in double show the order.
+static hipError_t apply_obs_lambda_tiles(sv_state psi, sv_state lam, const ObsPlan& op)
+{
+    const int n = psi->n, tq = std::min(n, kObsTileBits);
+    const uint64_t low = obs_tile_low(n, SV_C128);
+    const size_t n_off = op.oc.size();
+    hipStream_t s = psi->stream;
+    std::vector<char> done(n_off, 0);
+    std::vector<size_t> wide;
+    size_t d0 = 0;
+    int accumulate = 0;
+    hipError_t e = hipSuccess;
+    for (size_t k = 0; (k < n_off || d0 < op.dc.size()) && e == hipSuccess; ++k) {
+        if (k < n_off) {
+            if (done[k]) continue;
+            if (__builtin_popcountll(op.ox[k] | low) > tq) {
+                wide.push_back(k);
+                continue;
+            }
+        }
+        ObsTileBuild b;
+        obs_tile_take(n, op, done, k, k < n_off ? low : 0, d0, b);
+        e = launch_obs_tile_apply(psi->data, lam->data, n, b.ps, accumulate, s);
+        accumulate = 1;
+    }
+    if (!accumulate && e == hipSuccess)  // lambda = 0: an empty term list
+        e = launch_obs_diag_apply<double>(psi->data, lam->data, n, 0, 1.0, nullptr, nullptr, 0, 0, s);
+    for (size_t i = 0; i < wide.size() && e == hipSuccess; ++i) {
+        const size_t k = wide[i];
+        e = launch_obs_pauli_apply<double>(psi->data, lam->data, n, op.ox[k], op.oz[k], op.oy[k], op.oc[k], s);
+    }
+    return e;
+}
+
 template <typename T>
 static hipError_t apply_obs_lambda(sv_state psi, sv_state lam, const ObsPlan& op)
 {
+    if (sizeof(T) == sizeof(double) && !(op.diag_kind > 0 && op.oc.empty()))
+        return apply_obs_lambda_tiles(psi, lam, op);
     const int n = psi->n;
     hipStream_t s = psi->stream;
     hipError_t e;

@@ -71,6 +71,12 @@ struct GeneralSpec {  // dense 2^K x 2^K, all groups, no structure used
     T m[2 * (1 << K) * (1 << K)];
 };
 
+// v with its sign flipped where the lowest bit of `odd` is set.
+__device__ __forceinline__ double flip_if(double v, uint32_t odd)
+{
+    return __hiloint2double(__double2hiint(v) ^ (int)(odd << 31), __double2loint(v));
+}
+
 // Row a2 of the method on the device: group index -> base amplitude index.
 __device__ __forceinline__ uint64_t group_base(uint64_t g, const GroupSpec& gs)
 {
@@ -304,6 +310,9 @@ hipError_t launch_obs_diag_apply(const void* psi, void* lam, int n, int kind, do
 template <typename T>
 hipError_t launch_obs_pauli_apply(const void* psi, void* lam, int n, uint64_t xmask, uint64_t zmask,
                                   int ny, double coeff, hipStream_t s);
+// lam (=|+=) one pass's terms applied to psi, complex128.
+hipError_t launch_obs_tile_apply(const void* psi, void* lam, int n, const ObsTilePass& ps, int accumulate,
+                                 hipStream_t s);
 // Re <a|b> block partials (fp64).
 template <typename T>
 hipError_t launch_inner_partial(const void* a, const void* b, uint64_t n_amps, double* partials,
