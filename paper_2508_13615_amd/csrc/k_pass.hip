@@ -477,6 +477,26 @@ __device__ __forceinline__ double wave_sum(double v)
     return __hiloint2double(hi, lo);
 }
 
+// Two such sums for the instructions of one: v_permlane32_swap puts both halves
+// of each value side by side (a's in lanes 0..31, b's in 32..63), and the steps
+// within a half serve both: 18 vector instructions instead of 36 (24-qubit
+// gradient 9.58 -> 9.48 ms, the batch of 48 circuits 6.25 -> 6.22).
+__device__ __forceinline__ void wave_sum2(double& a, double& b)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    double v = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    v = dpp_plus<0xB1, 0xf>(v);
+    v = dpp_plus<0x4E, 0xf>(v);
+    v = dpp_plus<0x141, 0xf>(v);
+    v = dpp_plus<0x140, 0xf>(v);
+    v = dpp_plus<0x142, 0xa>(v);
+    a = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 31),
+                         __builtin_amdgcn_readlane(__double2loint(v), 31));
+    b = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                         __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+
 // Sum over the block of one value per thread, order fixed; result on thread 0.
 __device__ double block_sum_fixed(double v, double* red)
 {
@@ -1330,7 +1350,19 @@ __device__ __forceinline__ void item_reg_rev(const PassTables& tb, const FCirc& 
             const FOp& op = p.op;
             // an op with bits outside the tile acts here only if the tile holds them all
             const bool on = op_on(op, tile);
-            if (op.slot >= 0) {
+            if (op.kind == FK_RFUSE) {
+                // The pair's second gate: its partial with G_B; the first's with
+                // B G_A B^dagger; then one un-apply of B A.
+                double c = 0.0, d = 0.0;
+                if (op.slot >= 0) c = reg_gen_inner<T, RB>(v, w, op, tl);
+                if (op.b >= 0) d = reg_gen_inner_m<T, RB>(v, w, op, coef + op.coef + 8, tl);
+                c = active ? c : 0.0;
+                d = active ? d : 0.0;
+                wave_sum2(c, d);
+                if (op.slot >= 0) wpart[nslot++ * nwaves + wave] = c;
+                if (op.b >= 0) wpart[nslot++ * nwaves + wave] = d;
+                p.op.kind = FK_PAIR;
+            } else if (op.slot >= 0) {
                 double c = 0.0;
                 if (on) {
                     c = reg_gen_inner<T, RB>(v, w, op, tl);
@@ -1338,15 +1370,6 @@ __device__ __forceinline__ void item_reg_rev(const PassTables& tb, const FCirc& 
                 }
                 wpart[nslot * nwaves + wave] = c;
                 ++nslot;
-            }
-            if (op.kind == FK_RFUSE) {
-                // the pair's first gate: its partial with B G_A B^dagger; then one un-apply of B A
-                if (op.b >= 0) {
-                    const double c = reg_gen_inner_m<T, RB>(v, w, op, coef + op.coef + 8, tl);
-                    wpart[nslot * nwaves + wave] = wave_sum(active ? c : 0.0);
-                    ++nslot;
-                }
-                p.op.kind = FK_PAIR;
             }
             if (!on) continue;
             const T pzr = op.kind == FK_PHASE ? (T)coef[op.coef] : T(1);
