@@ -1406,7 +1406,8 @@ sv_status sv_tune_engine_get(int dtype, int with_grad, int* tile_qubits, int* am
 // issue) 31.4 / 32.8 / 34.5 and 26 qubits of mixed gates, whose 4x4 gates
 // sweep the tile in LDS, 6.41 / 6.93 / 6.86: those keep the tuned tile.  So do
 // states below 24 qubits, which the 256 MiB last-level cache holds: 21-qubit
-// HEA 0.423 / 0.410 / 0.417, 22-qubit QFT 0.205 / 0.210 / 0.225.
+// HEA 0.423 / 0.410 / 0.417, 22-qubit QFT 0.205 / 0.210 / 0.225.  27 qubits of
+// every other gate kind, three layers: 11.4 / 10.5 / 9.4.
 static sv_status plan_batch(const sv_batch_circuit* circuits, int n_circuits, int dtype, const sv_batch_opts* opts,
                             HostTables& H)
 {

@@ -24,6 +24,20 @@ def layers(n, depth):
     return ops, k
 
 
+def every_form(n, depth):
+    """All kinds that reach the rule: controlled gates, phases, swaps, dense and diagonal 2x2, far and near qubits."""
+    rng = np.random.default_rng(n)
+    ops, k = [Op("H", (), (q,)) for q in range(n)], 0
+    for _ in range(depth):
+        for q in range(n):
+            a, b = (int(x) for x in rng.choice([x for x in range(n) if x != q], size=2, replace=False))
+            ops += [Op("RX", (), (q,), k), Op("PHASE", (a,), (q,), k), Op("U2", (), (b,), -1, 0.0, W.haar_unitary(1, rng))]
+            ops += [Op("SWAP", (), (q, a))] if q % 5 == 0 else [Op("X", (a, b), (q,))] if q % 7 == 0 else []
+            k += 1
+        ops += [Op("RZ", (q,), (n - 1 - q,), q) for q in range(n // 2)]
+    return ops, k
+
+
 def test_rule():
     def passes(n, **kw):
         ops, k = layers(n, 4)
@@ -35,14 +49,14 @@ def test_rule():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n", [24, 25])
-def test_larger_tile_same_state(n):
-    ops, k = layers(n, 3)
+@pytest.mark.parametrize("n,form", [(24, layers), (25, layers), (24, every_form), (25, every_form)])
+def test_larger_tile_same_state(n, form):
+    ops, k = form(n, 3)
     theta = np.random.default_rng(n).uniform(-np.pi, np.pi, k)
     circuit = [(n, ops, k, "sum_zz")]
     a = sv.Batch(circuit, with_grad=False)
     b = sv.Batch(circuit, with_grad=False, tile_qubits=10)
-    assert a.info()["passes"] < b.info()["passes"]
+    assert a.info()["passes"] <= b.info()["passes"] - (form is layers)
     ea, eb = (float(np.asarray(x.run(theta)[0]).ravel()[0]) for x in (a, b))
     bar = 8 * len(ops) * np.finfo(np.float64).eps
     assert float((a.state_tensor(0) - b.state_tensor(0)).abs().max()) <= bar
