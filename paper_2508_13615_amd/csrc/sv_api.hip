@@ -1525,6 +1525,10 @@ static sv_status circuit_forward(sv_circuit c, sv_state st, const double* params
 
 // Whether a circuit's gates run in one workgroup (k_small_circuit): the state
 // fits its LDS, and there is more than one gate to share the round trip.
+// sv_circuit_apply only: this form applies and rounds every gate by itself,
+// while sv_circuit_apply_fused sums a diagonal run's angles first (and is the
+// faster of the two on such runs: 40 phases on 13 qubits complex128 7 us in
+// one pass, 57 us here).
 static bool small_circuit(const sv_circuit_s* c, const sv_state_s* st)
 {
     return c->ops.size() > 1 && (elem_bytes(st->dtype) << st->n) <= kSmallStateBytes;
@@ -1797,7 +1801,6 @@ sv_status sv_circuit_apply_fused(sv_circuit c_h, sv_state st_h, const double* pa
     SV_STATE(st);
     if (st->n != c->n) return set_error(SV_ERR_ARG, "state size does not match the circuit");
     if (c->n_params > 0 && !params) return set_error(SV_ERR_ARG, "null params");
-    if (small_circuit(c, st)) return circuit_forward_small(c, st, params);
     return circuit_forward_fused(c, st, params);
 }
 
