@@ -1529,9 +1529,20 @@ static sv_status circuit_forward(sv_circuit c, sv_state st, const double* params
 // while sv_circuit_apply_fused sums a diagonal run's angles first (and is the
 // faster of the two on such runs: 40 phases on 13 qubits complex128 7 us in
 // one pass, 57 us here).
+// On 2^14 amplitudes (complex64) loading and storing the state takes one
+// workgroup about 5 us and a 4x4 gate's sweep 4.3 us, as much as its own
+// launch, so the circuit needs three gates that are not 4x4 (us, launched /
+// here): two H 8.4 / 8.4, three 13.4 / 10.3, 24 91 / 47; 4x4 gates alone 2
+// 8.6 / 12.9, 8 33 / 38, 24 102 / 108.  On 2^13 amplitudes and fewer every
+// kind gains from two gates on (two 4x4, 13 qubits complex128 9.0 / 8.7).
 static bool small_circuit(const sv_circuit_s* c, const sv_state_s* st)
 {
-    return c->ops.size() > 1 && (elem_bytes(st->dtype) << st->n) <= kSmallStateBytes;
+    constexpr int kAnyQubits = 13, kLightOps = 3;
+    if (c->ops.size() < 2 || (elem_bytes(st->dtype) << st->n) > kSmallStateBytes) return false;
+    if (st->n <= kAnyQubits) return true;
+    int light = 0;
+    for (const OpRec& o : c->ops) light += o.gate != SV_U4 && o.gate != SV_I;
+    return light >= kLightOps;
 }
 
 static sv_status circuit_forward_small(sv_circuit c, sv_state st, const double* params)
