@@ -156,6 +156,48 @@ k_diag_obs_partial(const typename Vec2<T>::type* __restrict__ psi, uint64_t n_am
     if (threadIdx.x == 0) partials[blockIdx.x] = coeff * s;
 }
 
+struct DiagTerms {
+    int32_t nterms;
+    double c[kDiagTermsPerPass];
+    uint64_t z[kDiagTermsPerPass];
+};
+
+// o(x) = sum_k c_k (-1)^{pc(x & z_k)} per amplitude: nothing is staged, so a
+// few terms on a state that the last-level cache holds cost the least here
+// (diag_terms_direct says where); each further term is a popcount and an add
+// for every amplitude, where k_obs_tile pays one per thread and tile.
+template <typename T>
+__global__ void __launch_bounds__(kReduceThreads)
+k_diag_terms_partial(const typename Vec2<T>::type* __restrict__ psi, uint64_t n_amps, DiagTerms terms,
+                     double* __restrict__ partials)
+{
+    using V = typename Vec2<T>::type;
+    double acc = 0.0;
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x * 4;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x * 4 + threadIdx.x; i0 < n_amps + threadIdx.x;
+         i0 += stride) {
+        V a[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint64_t i = i0 + (uint64_t)j * blockDim.x;
+            if (i < n_amps) a[j] = psi[i];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint64_t x = i0 + (uint64_t)j * blockDim.x;
+            if (x < n_amps) {
+                double o = 0.0;
+                for (int k = 0; k < terms.nterms; ++k)
+                    o += (__popcll(x & terms.z[k]) & 1) ? -terms.c[k] : terms.c[k];
+                const double ar = (double)a[j].x, ai = (double)a[j].y;
+                acc += o * (ar * ar + ai * ai);
+            }
+        }
+    }
+    const double s = block_sum(acc);
+    if (threadIdx.x == 0) partials[blockIdx.x] = s;
+}
+
 // Many Pauli terms in one read of the state (ObsTilePass).  A term's xmask
 // lies inside the tile, so both amplitudes of each of its pairs are in the
 // workgroup's LDS copy; its zmask's bits outside the tile are one sign per
@@ -352,6 +394,24 @@ hipError_t launch_diag_obs_partial(const void* psi, int n, int kind, double coef
     return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_diag_terms_partial(const void* psi, int n, const double* hcoef, const uint64_t* hz, int nterms,
+                                     double* partials, hipStream_t s)
+{
+    using V = typename Vec2<T>::type;
+    DiagTerms terms{};
+    if (nterms > kDiagTermsPerPass) return hipErrorInvalidValue;
+    terms.nterms = nterms;
+    for (int k = 0; k < nterms; ++k) {
+        terms.c[k] = hcoef[k];
+        terms.z[k] = hz[k];
+    }
+    const uint64_t n_amps = 1ull << n;
+    hipLaunchKernelGGL((k_diag_terms_partial<T>), dim3(reduce_grid(n_amps)), dim3(kReduceThreads), 0, s,
+                       (const V*)psi, n_amps, terms, partials);
+    return hipGetLastError();
+}
+
 int obs_tile_blocks(int n)
 {
     const uint64_t tiles = n > kObsTileBits ? 1ull << (n - kObsTileBits) : 1ull;
@@ -394,6 +454,10 @@ template hipError_t launch_pauli_partial<float>(const void*, int, uint64_t, uint
                                                 hipStream_t);
 template hipError_t launch_diag_obs_partial<double>(const void*, int, int, double, double*, hipStream_t);
 template hipError_t launch_diag_obs_partial<float>(const void*, int, int, double, double*, hipStream_t);
+template hipError_t launch_diag_terms_partial<double>(const void*, int, const double*, const uint64_t*, int, double*,
+                                                      hipStream_t);
+template hipError_t launch_diag_terms_partial<float>(const void*, int, const double*, const uint64_t*, int, double*,
+                                                     hipStream_t);
 template hipError_t launch_obs_tile<double>(const void*, int, const ObsTilePass&, double*, hipStream_t);
 template hipError_t launch_obs_tile<float>(const void*, int, const ObsTilePass&, double*, hipStream_t);
 

@@ -1174,9 +1174,28 @@ static uint64_t obs_tile_low(int n, int dtype)
     return (1ull << std::min(n, dtype == SV_C128 ? 3 : 4)) - 1ull;
 }
 
+// Whether m diagonal terms with no off-diagonal one go through
+// k_diag_terms_partial instead of k_obs_tile.  Up to 256 MiB, where the
+// last-level cache holds the state, a tile pass takes 1 to 9 us longer to
+// start and to stage its tiles, while each term costs the per-amplitude kernel
+// more.  Whole calls, us, per amplitude / tiles: 12 qubits, 1 term 25.6 / 26.8,
+// 4 terms 26.0 / 27.3, 8 terms 27.3 / 27.8; 16 qubits, 1 term 24.8 / 27.0, 4
+// terms 26.2 / 27.4, 12 terms 29.3 / 28.8; 24 qubits complex128, 1 term 61.5 /
+// 70.2, 3 terms 65.4 / 71.1, 6 terms 82.3 / 71.7; complex64 1 term 54.2 / 60.7,
+// 3 terms 63.8 / 61.6, 4 terms 69.7 / 62.4; above 256 MiB tiles are faster from
+// the first term (29 qubits complex128 1523 / 1421).  A state of at most 256
+// amplitudes fills half of a tile's threads with one amplitude each: 8 qubits,
+// 8 terms 25.9 / 27.1, 32 terms 25.9 / 28.2; 6 qubits, 64 terms 30.0 / 31.3;
+// 9 qubits, 16 terms 26.9 / 28.3, 32 terms 29.4 / 30.4, 48 terms 33.3 / 30.1.
+static bool diag_terms_direct(int n, int dtype, size_t m)
+{
+    if (n <= 9) return n <= 8 || m <= (size_t)kDiagTermsPerPass;
+    return (elem_bytes(dtype) << n) <= (256ull << 20) && m <= (n <= 20 ? 4u : 3u);
+}
+
 // All passes of an observable.  A closed-form diagonal part with no other
-// term, and a lone off-diagonal term, keep their own one-read kernels
-// (measured equal to one tile pass); everything else goes through k_obs_tile,
+// term, a lone off-diagonal term, and diagonal terms as diag_terms_direct has
+// it keep their own one-read kernels; everything else goes through k_obs_tile,
 // which reads the state once for all the terms whose xmasks fit a tile.
 // 27 qubits complex128, the Heisenberg chain with a field (52 off-diagonal
 // and 53 diagonal terms): 3 reads of the state instead of 54, 2.5 ms instead
@@ -1193,6 +1212,15 @@ static hipError_t obs_passes_in(sv_state st, const P& op, Done& done, double* pa
     if (op.diag_kind > 0 && n_off == 0) {
         e = launch_diag_obs_partial<T>(st->data, n, op.diag_kind, op.diag_coeff, partials, st->stream);
         *count = reduce_blocks_for(1ull << n);
+        return e;
+    }
+    if (n_off == 0 && diag_terms_direct(n, st->dtype, n_diag)) {
+        for (size_t k0 = 0; k0 < n_diag && e == hipSuccess; k0 += kDiagTermsPerPass) {
+            const int nt = (int)std::min<size_t>(kDiagTermsPerPass, n_diag - k0);
+            e = launch_diag_terms_partial<T>(st->data, n, &op.dc[k0], &op.dz[k0], nt, partials + off, st->stream);
+            off += reduce_blocks_for(1ull << n);
+        }
+        *count = off;
         return e;
     }
     const uint64_t low = obs_tile_low(n, st->dtype);

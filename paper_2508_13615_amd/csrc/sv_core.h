@@ -247,7 +247,12 @@ hipError_t launch_pauli_partial(const void* psi, int n, uint64_t xmask, uint64_t
 // Diagonal observable in closed form, scaled by coeff: kind 1 = sum Z, 2 = sum ZZ.
 template <typename T>
 hipError_t launch_diag_obs_partial(const void* psi, int n, int kind, double coeff, double* partials, hipStream_t s);
-constexpr int kDiagTermsPerPass = 32;  // generic diagonal terms per k_obs_diag_apply launch
+constexpr int kDiagTermsPerPass = 32;  // generic diagonal terms per k_obs_diag_apply or k_diag_terms_partial launch
+// Diagonal observable sum_k c_k (-1)^{pc(x & z_k)}: at most kDiagTermsPerPass
+// host terms, passed by value in the kernel arguments.
+template <typename T>
+hipError_t launch_diag_terms_partial(const void* psi, int n, const double* hcoef, const uint64_t* hz, int nterms,
+                                     double* partials, hipStream_t s);
 
 // One reduction pass over many Pauli terms (k_obs_tile): the state is read
 // once, in tiles of 2^tq amplitudes that hold every bit of the pass's xmasks,
