@@ -257,7 +257,11 @@ typedef struct {
 
 /* Validate and copy an op list (matrices included) into a circuit object for
  * states of n_qubits.  Parameters are bound later, per run.  The circuit
- * holds a small device table of per-op gate coefficients. */
+ * holds device workspace for its gradient: up to 8 KiB for each parameterised
+ * op, and from the first complex128 sv_adjoint_grad on the pass engine's
+ * tables and its gradient partials (at most 64 MiB, or those of one pass, at
+ * most 1/32 of a state with the shipped engine shape).  sv_circuit_free gives
+ * all of it back. */
 sv_status sv_circuit_create(int n_qubits, const sv_op* ops, int n_ops, int n_params, sv_circuit* out);
 sv_status sv_circuit_free(sv_circuit c);
 

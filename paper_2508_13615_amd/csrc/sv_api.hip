@@ -2207,7 +2207,8 @@ static sv_status adjoint_sweep(sv_circuit c, sv_state psi, sv_state lam, const d
 }
 
 // The circuit's pass engine for complex128 gradients, or null where the
-// engine does not take the circuit (an op wider than a tile, or no room for
+// engine does not take the circuit (an op wider than a tile, a tile tuned so
+// small that a pass's gradient partials exceed half a state, or no room for
 // its tables): those, and complex64 gradients, walk op by op, one kernel per
 // op and state.  In complex64 the order in which gates are multiplied into
 // one another decides the last bits of the energy and the gradient, and op by

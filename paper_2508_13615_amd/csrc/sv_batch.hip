@@ -523,6 +523,14 @@ struct sv_batch_s {
     size_t lds_fwd, lds_rev;  // dynamic LDS of forward and reverse workgroups
     std::vector<int64_t> level_first;  // per level: forward, observable, reverse item ranges (4 bounds)
     std::vector<uint8_t> level_gated;  // per level: 1 if a forward pass of the level has FPass.gated set
+    // An engine's gradient sums: the passes of a group share the partials'
+    // memory with the other groups', and their slots are summed after the
+    // group's last level.
+    struct GradGroup {
+        size_t level_end;
+        int slot_begin, slot_end;
+    };
+    std::vector<GradGroup> grad_groups;  // in the order of the reverse levels
     int64_t n_items;
     int n_segs;
     int n_slots;
@@ -669,10 +677,16 @@ hipError_t enqueue_coef(sv_batch b, hipStream_t s)
     return e;
 }
 
+// Values of the slots [begin, end) from their per-tile partials.
+hipError_t enqueue_slot_sums(sv_batch b, int begin, int end, hipStream_t s)
+{
+    return launch_pass_segsum(b->d_gpart, b->d_g_off + begin, b->d_g_cnt + begin, b->d_slot_scale + begin,
+                              b->d_slot_val + begin, end - begin, nullptr, s);
+}
+
 hipError_t enqueue_grad_sums(sv_batch b, hipStream_t s)
 {
-    hipError_t e = launch_pass_segsum(b->d_gpart, b->d_g_off, b->d_g_cnt, b->d_slot_scale, b->d_slot_val, b->n_slots,
-                                      nullptr, s);
+    hipError_t e = enqueue_slot_sums(b, 0, b->n_slots, s);
     if (e == hipSuccess) e = launch_pass_grad_csr(b->d_slot_val, b->d_csr_ptr, b->d_csr_col, b->n_params, b->d_grads, s);
     return e;
 }
@@ -1458,6 +1472,65 @@ sv_status sv_batch_plan(const sv_batch_circuit* circuits, int n_circuits, sv_dty
     return SV_OK;
 }
 
+// Lays an engine's gradient partials out in groups of passes that reuse one
+// array of at most kGradGroupBytes, or of one pass where that is more (a pass
+// has at most kMaxPassSlots parameterised ops: with tiles of 2^10, 1/32 of a
+// complex128 state), so that what a circuit keeps beside the caller's states
+// does not grow with its gates.  Slots are renumbered in the order the reverse
+// passes fill them; each parameter still sums its slots in op order.  Costs a
+// sum launch (about 5 us) per group: 21 qubits and 168 parameterised gates are
+// 2.8 MB and one group, 30 qubits take a group per pass.
+static sv_status group_gradients(HostTables& H, std::vector<sv_batch_s::GradGroup>& groups)
+{
+    constexpr int64_t kGradGroupBytes = 64 << 20;
+    FCirc& fc = H.circs[0];
+    const int slots = (int)H.slot_param.size(), np = fc.n_pass;
+    const int64_t cap = std::max<int64_t>(1, kGradGroupBytes / (int64_t)sizeof(double) / fc.n_tiles);
+    std::vector<int> number(slots, -1);
+    std::vector<int64_t> off(slots);
+    int next = 0, first = 0;
+    int64_t largest = 0;
+    for (int p = np - 1; p >= 0; --p) {
+        const FPass& fp = H.passes[fc.pass_begin + p];
+        int64_t mine = 0;
+        for (int o = fp.rop_begin; o < fp.rop_end; ++o)
+            mine += (H.fops[o].slot >= 0) + (H.fops[o].kind == FK_RFUSE && H.fops[o].b >= 0);
+        if (next > first && next - first + mine > cap) {
+            groups.push_back({(size_t)(2 * np - p), first, next});
+            first = next;
+        }
+        auto place = [&](int32_t& slot) {
+            number[slot] = next;
+            slot = next - first;
+            off[next] = fc.g_part_begin + (int64_t)slot * fc.n_tiles;
+            ++next;
+        };
+        for (int o = fp.rop_begin; o < fp.rop_end; ++o) {
+            FOp& f = H.fops[o];
+            if (f.slot >= 0) place(f.slot);
+            if (f.kind == FK_RFUSE && f.b >= 0) place(f.b);
+        }
+        largest = std::max<int64_t>(largest, next - first);
+    }
+    groups.push_back({(size_t)(2 * np + 1), first, next});
+    if (next != slots) return set_error(SV_ERR_UNSUPPORTED, "internal: a parameterised op lies in no pass");
+    H.g_total = largest * fc.n_tiles;
+    // only a tile tuned far below 2^10 gets here
+    if (H.g_total * (int64_t)sizeof(double) > std::max<int64_t>(kGradGroupBytes, (int64_t)(H.state_total / 2)))
+        return set_error(SV_ERR_UNSUPPORTED, "gradient partials of a pass exceed half a state");
+    std::vector<double> scale(slots);
+    std::vector<int> param(slots);
+    for (int s = 0; s < slots; ++s) {
+        scale[number[s]] = H.slot_scale[s];
+        param[number[s]] = H.slot_param[s];
+    }
+    for (int& c : H.csr_col) c = number[c];
+    H.slot_scale = std::move(scale);
+    H.slot_param = std::move(param);
+    H.g_off = std::move(off);
+    return SV_OK;
+}
+
 // external: the states belong to the caller, who binds them for each run
 // (engine_forward); a run then starts from what psi holds, so nothing is
 // known to be zero.
@@ -1469,10 +1542,10 @@ static sv_status create_batch(const sv_batch_circuit* circuits, int n_circuits, 
         sv_status rc = plan_batch(circuits, n_circuits, dtype, opts, H);
         if (rc) return rc;
     }
+    std::vector<sv_batch_s::GradGroup> groups;
     if (external) {
-        // the gradient partials of all tiles stay within half of a state
-        if ((double)H.g_total * sizeof(double) > 0.5 * (double)H.state_total)
-            return set_error(SV_ERR_UNSUPPORTED, "gradient partials too large");
+        sv_status rc = group_gradients(H, groups);
+        if (rc) return rc;
         for (FCirc& c : H.circs) c.loaded = 1;
         for (FPass& p : H.passes) p.support = ~0ull;
     }
@@ -1521,6 +1594,7 @@ static sv_status create_batch(const sv_batch_circuit* circuits, int n_circuits, 
     b->n_rtabs = (int)dops.tabs.size();
     b->level_first = level_first;
     b->level_gated = H.level_gated;
+    b->grad_groups = std::move(groups);
     for (int c = 0; c < n_circuits; ++c) {
         b->nq.push_back(circs[c].n);
         b->max_passes = std::max(b->max_passes, circs[c].n_pass);
@@ -1590,7 +1664,7 @@ static sv_status create_batch(const sv_batch_circuit* circuits, int n_circuits, 
     A.table(&b->d_csr_col, csr_col);
     A.array(&b->d_coef, coef_total);
     if (dtype == SV_C64) A.array(&b->d_coef_f, coef_total);
-    A.array(&b->d_epart, e_total);
+    A.array(&b->d_epart, external ? 0 : e_total);  // an engine's caller takes the observable
     A.array(&b->d_echunk, ec_off.size());
     A.array(&b->d_gpart, g_total);
     A.array(&b->d_slot_val, slot_param.size());
@@ -1678,8 +1752,14 @@ hipError_t engine_forward(sv_batch_s* b, void* psi, void* lam, const double* par
 
 hipError_t engine_reverse(sv_batch_s* b, hipStream_t s, const double** grads)
 {
-    hipError_t e = enqueue_levels(b, b->max_passes + 1, b->n_levels, s);  // the observable's level is the caller's
-    if (e == hipSuccess) e = enqueue_grad_sums(b, s);
+    hipError_t e = hipSuccess;
+    size_t level = b->max_passes + 1;  // the observable's level is the caller's
+    for (const sv_batch_s::GradGroup& g : b->grad_groups) {
+        if (e == hipSuccess) e = enqueue_levels(b, level, g.level_end, s);
+        if (e == hipSuccess) e = enqueue_slot_sums(b, g.slot_begin, g.slot_end, s);
+        level = g.level_end;
+    }
+    if (e == hipSuccess) e = launch_pass_grad_csr(b->d_slot_val, b->d_csr_ptr, b->d_csr_col, b->n_params, b->d_grads, s);
     *grads = b->d_grads;
     return e;
 }
