@@ -24,6 +24,7 @@
 #include <cstdlib>
 #include <cstdio>
 #include <mutex>
+#include <new>
 #include <string>
 #include <unordered_set>
 #include <vector>
@@ -2218,8 +2219,8 @@ static sv_status adjoint_sweep(sv_circuit c, sv_state psi, sv_state lam, const d
 static sv_batch_s* adjoint_engine(sv_circuit c, int dtype)
 {
     if (dtype != SV_C128) return nullptr;
-    if (!c->engine_tried) {
-        c->engine_tried = true;
+    if (c->engine_tried) return c->engine;
+    try {
         std::vector<sv_op> ops(c->ops.size());
         for (size_t i = 0; i < ops.size(); ++i) {
             const OpRec& o = c->ops[i];
@@ -2233,7 +2234,9 @@ static sv_batch_s* adjoint_engine(sv_circuit c, int dtype)
             s.value = o.value;
             s.matrix = o.matrix.empty() ? nullptr : o.matrix.data();
         }
-        c->engine = engine_create(c->n, ops.data(), (int)ops.size(), c->n_params, dtype);
+        // no memory now is not no memory later: the next gradient tries again
+        c->engine_tried = engine_create(c->n, ops.data(), (int)ops.size(), c->n_params, dtype, &c->engine) != SV_ERR_OOM;
+    } catch (const std::bad_alloc&) {  // planning found no host memory: this gradient walks op by op
     }
     return c->engine;
 }

@@ -627,9 +627,9 @@ struct TableArena {
                 }
             if (want_small) staged = total;
         }
+        std::vector<char> host(staged);
         hipError_t e = hipMalloc(base, total);
         if (e != hipSuccess) return e;
-        std::vector<char> host(staged);
         for (const Item& it : items) {
             *it.dst = (char*)*base + it.off;
             if (!it.src || !it.bytes) continue;
@@ -1728,13 +1728,12 @@ sv_status sv_batch_create(const sv_batch_circuit* circuits, int n_circuits, sv_d
 
 namespace svk {
 
-sv_batch_s* engine_create(int n, const sv_op* ops, int n_ops, int n_params, int dtype)
+sv_status engine_create(int n, const sv_op* ops, int n_ops, int n_params, int dtype, sv_batch_s** out)
 {
     const sv_batch_circuit c{n, n_ops, ops, n_params, 1};
     sv_batch_opts o{};
     o.with_grad = 1;
-    sv_batch_s* b = nullptr;
-    return create_batch(&c, 1, (sv_dtype)dtype, &o, true, &b) == SV_OK ? b : nullptr;
+    return create_batch(&c, 1, (sv_dtype)dtype, &o, true, out);
 }
 
 void engine_free(sv_batch_s* b) { batch_release(b); }

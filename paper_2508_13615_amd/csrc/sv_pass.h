@@ -255,14 +255,15 @@ size_t pass_engine_lds_bytes(int tq_max, int hi_entries, int with_grad, int dtyp
 int pass_engine_threads(int tq_max, int reg_bits);
 
 // The engine on a caller's states (the adjoint sweep of a circuit object):
-// engine_create returns null where the engine does not take the circuit.
+// engine_create reports why an engine does not take the circuit (SV_ERR_OOM:
+// no room for its tables just now; else it never will).
 // engine_forward runs every forward pass on psi; the caller then forms lambda
 // = O psi; engine_reverse walks back, leaving psi as it was and the gradient
 // in device memory.  All on stream s; a run at a time per engine.
 }  // namespace svk
 struct sv_batch_s;
 namespace svk {
-sv_batch_s* engine_create(int n, const sv_op* ops, int n_ops, int n_params, int dtype);
+sv_status engine_create(int n, const sv_op* ops, int n_ops, int n_params, int dtype, sv_batch_s** out);
 void engine_free(sv_batch_s* b);
 hipError_t engine_forward(sv_batch_s* b, void* psi, void* lam, const double* params, hipStream_t s);
 hipError_t engine_reverse(sv_batch_s* b, hipStream_t s, const double** grads);
