@@ -2213,12 +2213,20 @@ static sv_status adjoint_sweep(sv_circuit c, sv_state psi, sv_state lam, const d
 // its tables): those, and complex64 gradients, walk op by op, one kernel per
 // op and state.  In complex64 the order in which gates are multiplied into
 // one another decides the last bits of the energy and the gradient, and op by
-// op is what complex64 callers have always got.  21 qubits, 4 layers of the
-// HEA, the transverse-field Ising chain: 1.24 ms, 7.95 ms op by op (the first
-// call, which plans, 1.55 ms).
+// op is what complex64 callers have always got.  So do circuits of a gate or
+// two on small states, where the engine's extra launches and table copies show
+// (whole calls, us, op by op / engine): one gate, 12 qubits 85 / 95, 20 qubits
+// 95 / 124, 23 qubits 248 / 288, 24 qubits 523 / 529 (662 / 562 with an
+// off-diagonal observable); two gates, 20 qubits 110 / 119, 21 qubits 145 /
+// 141; three gates, 6 qubits 99 / 98, 20 qubits 132 / 128, 24 qubits 1078 /
+// 538.  21 qubits, 4 layers of the HEA, the transverse-field Ising chain:
+// 0.98 ms, 7.95 ms op by op (the first call, which plans, about 0.3 ms more).
 static sv_batch_s* adjoint_engine(sv_circuit c, int dtype)
 {
     if (dtype != SV_C128) return nullptr;
+    int gates = 0;
+    for (const OpRec& o : c->ops) gates += o.gate != SV_I;
+    if (gates < (c->n <= 20 ? 3 : c->n <= 23 ? 2 : 1)) return nullptr;
     if (c->engine_tried) return c->engine;
     try {
         std::vector<sv_op> ops(c->ops.size());
