@@ -24,6 +24,8 @@
 // a hipGraph and replayed.  (An earlier single persistent kernel synchronised
 // stages with device-scope counters; on this multi-XCD part each acquire poll
 // invalidates the L2, so waiting workgroups throttled the working ones.)
+#include <mutex>
+
 #include "sv_core.h"
 #include "sv_pass.h"
 
@@ -1870,10 +1872,14 @@ size_t pass_engine_lds_bytes(int tq_max, int hi_entries, int with_grad, int dtyp
 }
 
 // The dynamic-LDS limit only grows: batches that are alive at the same time
-// launch the same kernels with different LDS sizes.
+// launch the same kernels with different LDS sizes.  The lock covers the
+// calls that raise it: of two threads the one that asks for less could set the
+// kernels' limit last, below what the other one launches with.
 hipError_t pass_engine_prepare(size_t lds_bytes)
 {
+    static std::mutex mu;
     static size_t limit = 0;
+    std::lock_guard<std::mutex> lk(mu);
     if (lds_bytes <= limit) return hipSuccess;
     const void* f[] = {(const void*)k_pass_fwd<double, 3, false>, (const void*)k_pass_fwd<double, 4, false>,
                        (const void*)k_pass_fwd<double, 3, true>,  (const void*)k_pass_fwd<double, 4, true>,
