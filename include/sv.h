@@ -387,9 +387,11 @@ sv_status sv_batch_set_stream(sv_batch b, void* stream);
 sv_status sv_batch_plan(const sv_batch_circuit* circuits, int n_circuits, sv_dtype dtype,
                         const sv_batch_opts* opts, int64_t* info);
 
-/* info[0..11]: circuits, work items, passes, max passes per circuit, gate
- * ops scheduled, parameters, state bytes, algorithmic HBM bytes per run,
- * stage levels (each launches up to three kernels: forward, observable and
+/* info[0..11]: circuits, work items (tiles of every stage; the observable is
+ * a stage also where a forward-only run takes it in its last pass), passes,
+ * max passes per circuit, gate ops scheduled, parameters, state bytes, HBM
+ * bytes of the states that a run loads and stores (amplitudes still zero when
+ * a pass begins are neither, until the last pass), stage levels (each launches up to three kernels: forward, observable and
  * reverse items), LDS bytes per workgroup, layout changes in the forward
  * passes (each an LDS exchange of every tile), workgroup size of forward
  * passes. */

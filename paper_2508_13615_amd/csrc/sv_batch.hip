@@ -919,7 +919,6 @@ static sv_status compile_batch(const sv_batch_circuit* circuits, int n_circuits,
     int64_t g_total = 0;
     int e_total = 0;
     size_t state_total = 0;
-    double pass_bytes = 0;
     const size_t eb = dtype == SV_C128 ? 16 : 8;
     size_t all_ops = 0;
     for (int c = 0; c < n_circuits; ++c) all_ops += (size_t)std::max(0, circuits[c].n_ops);
@@ -1097,8 +1096,25 @@ static sv_status compile_batch(const sv_batch_circuit* circuits, int n_circuits,
         psi_off[c] = state_total;
         const size_t sb = ((size_t)1 << n) * eb;
         state_total += (sb + 255) & ~(size_t)255;
-        pass_bytes += 2.0 * (double)sb * (with_grad ? 3.0 * fc.n_pass + 1.0 : fc.n_pass + 0.5);
     }
+
+    // ---- HBM bytes of a run: what its kernels load and store of the states ----
+    // A forward pass of register tiles loads the amplitudes of its support and
+    // stores the tiles that hold any, the last pass every amplitude; the first
+    // one loads nothing.  A forward-only run of such circuits takes the
+    // observable from the last pass's registers, else the observable reads
+    // the state (and writes lambda); a reverse pass reads and writes both.
+    double pass_bytes = 0;
+    for (const FCirc& c : circs)
+        for (int p = 0; p < c.n_pass; ++p) {
+            const FPass& fp = passes[c.pass_begin + p];
+            const double na = (double)(c.all_bits + 1);
+            const double load = !c.reg ? na : (double)(1ull << popc(fp.support));
+            const double store = !c.reg ? na : (double)(1ull << popc(fp.support | (c.all_bits & ~fp.free_mask)));
+            pass_bytes += (double)eb * ((p ? load : 0.0) + (p + 1 < c.n_pass ? store : na));
+            if (with_grad) pass_bytes += (double)eb * 4.0 * na;
+            if (p + 1 == c.n_pass) pass_bytes += (double)eb * (with_grad ? 2.0 * na : lds_small ? na : 0.0);
+        }
 
     // ---- work segments, level-major: stage s of every circuit before stage s+1;
     //      inside a level forward stages, then observable stages, then reverse ----

@@ -220,7 +220,6 @@ def engine_bounds(bench_line: str, runs: dict, n: int = 30, layers: int = 10) ->
     # forward pass kernels of 16 amplitudes per thread, both instances (with and
     # without the out-of-tile control test), summed
     kern = {"c128": "k_pass_fwd<double, 4", "c64": "k_pass_fwd<float, 4"}
-    ebytes = {"c128": 16, "c64": 8}
     rows = ["| circuit | dtype | s per run (HIP events) | passes | gate ops (fused) | layout changes | "
             "HBM floor at 8 TB/s | VALU issue floor | VALU / wave / pass | SALU / wave / pass | VALU busy |",
             "|---|---|---|---|---|---|---|---|---|---|---|"]
@@ -239,7 +238,7 @@ def engine_bounds(bench_line: str, runs: dict, n: int = 30, layers: int = 10) ->
                         c[cn] = c.get(cn, 0.0) + cv
             plan = sv.batch_plan([(n, ops, len(th), "sum_z")], dt, with_grad=False)
             t = secs[f"{name}_{dt}"]
-            hbm = (2 * plan["passes"] + 1) * (1 << n) * ebytes[dt] / 8e12
+            hbm = plan["pass_bytes"] / 8e12
             valu = c["SQ_INSTS_VALU"] / 4 * 4 / (1024 * 2.4e9)
             rows.append(f"| {name} | {dt} | {t:.4f} | {plan['passes']} | {plan['fused_ops']} | "
                         f"{plan['layout_changes']} | {hbm:.4f} s | {valu:.4f} s | "
