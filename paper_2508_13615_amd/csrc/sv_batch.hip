@@ -1384,12 +1384,24 @@ static DeviceOps device_ops(HostTables& H)
     return D;
 }
 
-// Largest dynamic LDS a workgroup of the batch uses (reverse passes hold the
-// per-slot wave partials on top of the forward layout).
-static size_t engine_lds_max(const HostTables& H, int dtype)
+// Dynamic LDS of a batch's workgroups.  Reverse passes hold the per-slot wave
+// partials on top of the tile; the complex128 forward exchange needs half a
+// tile unless some op or circuit works on a tile in LDS.
+struct EngineLdsBytes {
+    size_t fwd, rev;
+    int half;
+    size_t max() const { return std::max(fwd, rev); }
+};
+static EngineLdsBytes engine_lds_bytes(const HostTables& H, int dtype)
 {
-    return pass_engine_lds_bytes(H.tq_used, H.hi_entries, H.with_grad, dtype, H.lds_small,
-                                 H.with_grad ? H.rthreads / 64 : 0);
+    EngineLdsBytes l;
+    l.half = dtype == SV_C128 && !H.lds_small;
+    for (const FPass& fp : H.passes)
+        for (int o = fp.op_begin; o < fp.op_end; ++o)
+            if (H.fops[o].kind == FK_QUAD) l.half = 0;
+    l.fwd = pass_engine_lds_bytes(H.tq_used, H.hi_entries, H.with_grad, dtype, H.lds_small, 0) >> l.half;
+    l.rev = H.with_grad ? pass_engine_lds_bytes(H.tq_used, H.hi_entries, 1, dtype, H.lds_small, H.rthreads / 64) : 0;
+    return l;
 }
 
 sv_status sv_tune_engine_set(int dtype, int with_grad, int tile_qubits, int amps_per_thread)
@@ -1482,7 +1494,7 @@ sv_status sv_batch_plan(const sv_batch_circuit* circuits, int n_circuits, sv_dty
     info[6] = (int64_t)H.state_total;
     info[7] = (int64_t)H.pass_bytes;
     info[8] = H.n_levels;
-    info[9] = (int64_t)engine_lds_max(H, dtype);
+    info[9] = (int64_t)engine_lds_bytes(H, dtype).max();
     info[10] = H.n_layout_changes;
     info[11] = H.threads;
     return SV_OK;
@@ -1565,6 +1577,7 @@ static sv_status create_batch(const sv_batch_circuit* circuits, int n_circuits, 
         for (FCirc& c : H.circs) c.loaded = 1;
         for (FPass& p : H.passes) p.support = ~0ull;
     }
+    const EngineLdsBytes lds = engine_lds_bytes(H, dtype);
     const DeviceOps dops = device_ops(H);
     const int with_grad = H.with_grad, threads = H.threads, n_params = H.n_params, coef_total = dops.coef_total;
     const int tq_used = H.tq_used, hi_entries = H.hi_entries, e_total = H.e_total;
@@ -1714,14 +1727,10 @@ static sv_status create_batch(const sv_batch_circuit* circuits, int n_circuits, 
     tb.lds_small = H.lds_small;
     // a forward-only run whose circuits are all register-tiled takes the observable in its last passes
     tb.fuse_obs = !with_grad && !H.lds_small;
-    // the forward exchange needs half a tile unless some op or circuit works on a tile in LDS
-    tb.lds_half = dtype == SV_C128 && !H.lds_small;
-    for (const FPass& fp : passes)
-        for (int o = fp.op_begin; o < fp.op_end; ++o)
-            if (dops.ops[o].kind == FK_QUAD) tb.lds_half = 0;
-    b->lds_fwd = pass_engine_lds_bytes(tq_used, hi_entries, with_grad, dtype, H.lds_small, 0) >> tb.lds_half;
-    b->lds_rev = pass_engine_lds_bytes(tq_used, hi_entries, with_grad, dtype, H.lds_small, H.rthreads / 64);
-    e = pass_engine_prepare(engine_lds_max(H, dtype));
+    tb.lds_half = lds.half;
+    b->lds_fwd = lds.fwd;
+    b->lds_rev = lds.rev;
+    e = pass_engine_prepare(lds.max());
     if (e != hipSuccess) {
         batch_release(b);
         return hip_fail(e, "pass engine LDS limit");
@@ -1860,7 +1869,7 @@ sv_status sv_batch_info(sv_batch b_h, int64_t* info)
     info[6] = (int64_t)b->state_bytes;
     info[7] = (int64_t)b->pass_bytes;
     info[8] = b->n_levels;
-    info[9] = (int64_t)std::max(b->lds_fwd, b->with_grad ? b->lds_rev : 0);
+    info[9] = (int64_t)std::max(b->lds_fwd, b->lds_rev);
     info[10] = b->n_layout_changes;
     info[11] = b->threads;
     return SV_OK;

@@ -46,3 +46,17 @@ def test_full_size_runs_move_no_more_than_every_pass_whole(name):
 def test_states_below_a_register_tile_move_whole():
     n = 2  # below 2^3 amplitudes: the observable is a stage of its own
     assert plan(n, [Op("H", (), (0,))])["pass_bytes"] == 2 * (16 << n)
+
+
+@pytest.mark.parametrize("dtype,tile,grad,u4,expect", [
+    ("c128", 12, False, False, 2 ** 11 * 16),  # complex128 forward passes exchange through half a tile
+    ("c128", 12, False, True, 2 ** 12 * 16),   # a 4x4 gate sweeps the tile in LDS
+    ("c64", 12, False, False, 2 ** 12 * 8),
+    ("c128", 10, True, False, 2 ** 10 * 16 + 8 * 64 * 2),  # reverse: a tile and 64 slots of 2 wavefronts
+])
+def test_lds_bytes(dtype, tile, grad, u4, expect):
+    ops = W.hea_ops(14, 1)
+    if u4:
+        ops = ops + [Op("U4", (), (0, 1), -1, 0.0, [[float(i == j) for j in range(4)] for i in range(4)])]
+    p = plan(14, ops, W.hea_n_params(14, 1), dtype, grad=grad, tile_qubits=tile, amps_per_thread=16)
+    assert p["lds_bytes"] == expect
