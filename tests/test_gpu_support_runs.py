@@ -84,3 +84,27 @@ def test_not_a_number_spreads_to_zero_amplitudes(dtype):
     ref = oracle.run_circuit(oracle.zero_state(n), ops, [0.3])
     assert float(np.max(np.abs(b.state(0) - ref))) <= 1e-6
     assert abs(e[0] - oracle.expval_obs(ref, W.sum_z(n))) <= 1e-5
+
+
+def second_byte(n, rng, across):
+    """One run onto qubit 3 with tiles of qubits 0..4: pairs of controls inside byte 1 of the tile index (qubits 13 and
+    up) and inside byte 0, which is a run of tables; with `across`, one pair with a control in each byte, which is not."""
+    pairs = [(13, 14), (14, n - 1), (13, n - 1), (5, 9), (6, 12)] + ([(7, 15)] if across else [])
+    ops = [Op("RY", (), (q,), -1, float(rng.uniform(0, 6))) for q in range(n)]
+    ops += [Op("PHASE", p, (3,), -1, float(rng.uniform(0, 6))) for p in pairs]
+    ops += [Op("PHASE", (q,), (3,), -1, float(rng.uniform(0, 6))) for q in range(n) if q != 3]
+    return ops + [Op("H", (), (3,))]
+
+
+@pytest.mark.parametrize("form", ["within", "across", "two_controls", "fourier"])
+@pytest.mark.parametrize("n", [16, 17])
+@pytest.mark.parametrize("tile,apt", [(5, 8), (6, 16)])
+@pytest.mark.parametrize("dtype,tol", [("c128", 1e-12), ("c64", 1e-5)])
+def test_tile_indices_of_two_bytes(form, n, tile, apt, dtype, tol):
+    rng = np.random.default_rng(4)
+    ops = FORMS[form](n, rng) if form in FORMS else second_byte(n, rng, form == "across")
+    ref = oracle.run_circuit(oracle.zero_state(n), ops)
+    b = sv.Batch([(n, ops, 0, "sum_z")], dtype=dtype, tile_qubits=tile, amps_per_thread=apt, with_grad=False)
+    e, _ = b.run([])
+    assert float(np.max(np.abs(b.state(0) - ref))) <= tol
+    assert abs(e[0] - oracle.expval_obs(ref, W.sum_z(n))) <= tol * n
