@@ -219,14 +219,15 @@ sv_status sv_expval_obs_dev(sv_state st, const sv_obs* obs, double* out_dev);
  * (512 KiB).  No hipMalloc, hipFree or other allocating device call is
  * made, and on success the host side allocates nothing either (only an
  * error's message does).
- * Limit: the observable may need at most 64 reduction passes (one per off-
- * diagonal term, one per 32 diagonal terms, one for sum Z_i or
- * sum Z_i Z_i+1); larger ones are rejected with SV_ERR_ARG before any device
- * work.  The state must live on the current device.  Every call on a GPU
+ * Limit: at most 64, counting one for each off-diagonal term, one for each
+ * 32 diagonal terms (begun) and one for all of sum Z_i or sum Z_i Z_i+1;
+ * larger observables are rejected with SV_ERR_ARG before any device work
+ * (a bound on the term list, not on the reads of the state, which are fewer).
+ * The state must live on the current device.  Every call on a GPU
  * shares that GPU's array: calls that overlap on one GPU (different streams
  * or threads without ordering between them) race and give wrong values.
  * Asynchronous on the state's stream.
- * Errors: as sv_expval_obs_dev, SV_ERR_ARG for too many passes. */
+ * Errors: as sv_expval_obs_dev, SV_ERR_ARG for too many terms. */
 sv_status sv_expval_obs_dev_noalloc(sv_state st, const sv_obs* obs, double* out_dev);
 
 /* <psi|P|psi> of one Pauli string (as sv_expval_pauli) written to device
@@ -351,7 +352,9 @@ typedef struct {
 } sv_batch_circuit;
 
 typedef struct {
-    int32_t tile_qubits; /* 0 = the engine shape (sv_tune_engine_set), else 2..13 */
+    int32_t tile_qubits; /* 0 = the engine shape (sv_tune_engine_set; where that is 2^10 x 16, a
+                          * forward-only complex128 batch of one circuit of 24 or more qubits may
+                          * take up to 2^12 if that saves passes), else 2..13 */
     int32_t amps_per_thread; /* 0 = the engine shape; 8 or 16: amplitudes of a tile each thread
                               * holds in registers (workgroup = 2^tile_qubits / this, >= 64) */
     int32_t use_graph;   /* capture the run on first use, replay afterwards */

@@ -246,7 +246,8 @@ class State:
     def expval_dev_noalloc(self, obs, out: torch.Tensor) -> None:
         """As expval_dev with no device allocation: the partials live in the
         library's static per-GPU array (sv_expval_obs_dev_noalloc; at most 64
-        reduction passes; overlapping calls on one GPU race)."""
+        off-diagonal terms, 32 diagonal ones counting as one; overlapping calls
+        on one GPU race)."""
         obs = obs if isinstance(obs, Observable) else Observable(obs)
         check(lib.sv_expval_obs_dev_noalloc(self.handle, ctypes.byref(obs.c), ctypes.c_void_p(out.data_ptr())))
 
@@ -442,8 +443,9 @@ class AdjointExpval(torch.autograd.Function):
     gradient from one backward sweep instead of per-parameter reruns.
 
     Two forms:
-      * AdjointExpval.apply(params, circuit, psi, lam, obs): a Circuit run op
-        by op on the states psi and lam (any observable).  The C entry point
+      * AdjointExpval.apply(params, circuit, psi, lam, obs): a Circuit run on
+        the states psi and lam (any observable): the gradient in fused passes
+        in complex128, op by op in complex64.  The C entry point
         takes host parameters, so params are copied to the host.  When no
         gradient is needed (params does not require one, or under
         torch.no_grad) only the forward pass and the expectation run, outside

@@ -974,10 +974,9 @@ sv_status sv_norm2(sv_state st_h, double* out)
     return finish_scalar(st, res, out);
 }
 
-// An observable split into diagonal terms (xmask = 0: one pass evaluates up
-// to kDiagTermsPerPass of them, or the closed forms sum Z_i / sum Z_i Z_i+1
-// in one) and off-diagonal terms (one pass each).  The term lists are
-// std::vector here and fixed-capacity arrays in the allocation-free plan.
+// An observable split into diagonal terms (xmask = 0) and off-diagonal terms;
+// obs_passes_in says which kernel takes which.  The term lists are std::vector
+// here and fixed-capacity arrays in the allocation-free plan.
 template <typename T, int N>
 struct FixedVec {
     T v[N];
@@ -1011,9 +1010,7 @@ struct ObsPlan {
     std::vector<int> oy;
 };
 
-// Term capacity of the allocation-free plan: at most kNoAllocPasses
-// reduction passes, each a pass of up to kDiagTermsPerPass diagonal terms or
-// one off-diagonal term.
+// Term capacity of the allocation-free plan: obs_pass_count at most this.
 constexpr int kNoAllocPasses = 64;
 struct ObsPlanFixed {
     int diag_kind;
@@ -1067,8 +1064,8 @@ static sv_status plan_obs(int n, const sv_obs* obs, P* op)
                  add_term(op->oy, (int)__builtin_popcountll(x & z));
         }
         if (!ok)  // only the fixed-capacity plan can run out of room
-            return set_error(SV_ERR_ARG, "observable needs more reduction passes than this entry point holds (" +
-                                             std::to_string(kNoAllocPasses) + ")");
+            return set_error(SV_ERR_ARG, "observable longer than the " + std::to_string(kNoAllocPasses) +
+                                             " term passes this entry point holds (1 off-diagonal or 32 diagonal terms each)");
     }
     if (!op->dc.empty()) {
         op->diag_kind = closed_form(n, op->dc, op->dz);
@@ -1077,7 +1074,11 @@ static sv_status plan_obs(int n, const sv_obs* obs, P* op)
     return SV_OK;
 }
 
-// Reduction passes of a plan (each writes one stage-1 grid of partials).
+// Size of an observable against kNoAllocPasses: one for each off-diagonal
+// term, one for each 32 diagonal terms, one for a closed form.  No way of
+// taking the terms writes more stage-1 grids of partials than this
+// (obs_passes_in mostly writes far fewer: a tile pass takes up to 48
+// off-diagonal and 64 diagonal terms).
 template <typename P>
 static int obs_pass_count(const P& op)
 {
@@ -1337,8 +1338,8 @@ sv_status sv_expval_obs_dev_noalloc(sv_state st_h, const sv_obs* obs, double* ou
     sv_status rc = plan_obs(st->n, obs, &op);
     if (rc) return rc;
     if (obs_pass_count(op) > kNoAllocPasses)
-        return set_error(SV_ERR_ARG, "observable needs " + std::to_string(obs_pass_count(op)) +
-                                         " reduction passes; this entry point holds at most " +
+        return set_error(SV_ERR_ARG, "observable of " + std::to_string(obs_pass_count(op)) +
+                                         " term passes (1 off-diagonal or 32 diagonal terms each); this entry point holds at most " +
                                          std::to_string(kNoAllocPasses));
     double* partials = nullptr;
     rc = scratch_dev(&partials);

@@ -1441,15 +1441,22 @@ sv_status sv_tune_engine_get(int dtype, int with_grad, int* tile_qubits, int* am
 // A batch's plan.  A forward-only complex128 run of one large circuit may take
 // a larger tile than the tuned one where that saves passes: its passes are
 // bound by HBM when they hold few ops each, so the tile of 10 to 12 qubits
-// with the fewest passes wins (ties: the smaller).  Measured at 16 amplitudes
-// per thread, tiles of 10 / 11 / 12: 29-qubit HEA (13 ops a pass) 91.3 / 80.8 /
-// 82.3 ms, 26-qubit HEA 9.98 / 6.92 / 7.62, 24-qubit HEA 1.54 / 1.67 / 1.40;
-// but the 28-qubit universal circuit (60 ops a pass, bound by instruction
-// issue) 31.4 / 32.8 / 34.5 and 26 qubits of mixed gates, whose 4x4 gates
-// sweep the tile in LDS, 6.41 / 6.93 / 6.86: those keep the tuned tile.  So do
-// states below 24 qubits, which the 256 MiB last-level cache holds: 21-qubit
-// HEA 0.423 / 0.410 / 0.417, 22-qubit QFT 0.205 / 0.210 / 0.225.  27 qubits of
-// every other gate kind, three layers: 11.4 / 10.5 / 9.4.
+// with the fewest passes wins (ties: the smaller).  ms at 16 amplitudes per
+// thread, tiles of 10 / 11 / 12, * the one taken:
+//   qubits          24                  26                  28                  29
+//   HEA, 4 layers   .928 .955 .859*     4.24 3.47 3.33*     16.0 14.8 14.2*     33.9 30.2* 32.4
+//   HEA, 10 layers  2.53 2.57 2.51*     11.9 9.20 9.22*     44.7 38.3 40.3*     91.2 81.0* 83.9
+//   QFT             .265* .308 .334     .873 .757* .979     3.33 3.17 2.80*     6.79 6.86 5.43*
+// (25 and 27 qubits and the GHZ ladder likewise): never slower than 2^10, at
+// most 5% from the best.  The tuned tile stays for circuits with 4x4 gates,
+// which sweep the tile in LDS (26 qubits of mixed gates 6.41 / 6.93 / 6.86),
+// for more than 24 ops a pass, which are bound by instruction issue (28-qubit
+// universal circuit, 60 ops a pass, 31.4 / 32.8 / 34.5), and below 24 qubits,
+// where the 256 MiB last-level cache holds the state (22-qubit QFT 0.205 /
+// 0.210 / 0.225).  complex64 keeps its tuned 2^11: there the larger tiles'
+// passes cost more than the saved ones (tiles of 11 / 12 / 13, HEA of 4 layers
+// on 28 qubits 9.57 / 10.8 / 10.0 in 12, 12 and 10 passes, on 30 qubits 41.9 /
+// 46.2 / 46.0; the 30-qubit QFT would gain, 12.8 / 12.6 / 10.8).
 static sv_status plan_batch(const sv_batch_circuit* circuits, int n_circuits, int dtype, const sv_batch_opts* opts,
                             HostTables& H)
 {
