@@ -121,8 +121,10 @@ enum IpMode : int {
 // Complex 2x2 (row-major, interleaved u): a, b <- u (a, b).  In single
 // precision each result is the sum of two products of complex numbers, each
 // rounded once (five instructions a component); in double precision one
-// multiply and three fused multiply-adds.
-template <typename T, int M, typename V>
+// multiply and three fused multiply-adds.  RE_FIRST (single precision): the
+// imaginary parts round u's real part times y before the sum, else u's
+// imaginary part times x.
+template <typename T, int M, bool RE_FIRST = false, typename V>
 __device__ __forceinline__ void pair_ip(const T* u, V& a, V& b, uint64_t ok)
 {
 #define SV_IN(C)                                                                                                   \
@@ -153,6 +155,22 @@ __device__ __forceinline__ void pair_ip(const T* u, V& a, V& b, uint64_t ok)
 #undef SV_BODY
     } else {
         T n0, n1, n2, n3;
+#define SV_OUT8 SV_OUT, [n0] "=&v"(n0), [n1] "=&v"(n1), [n2] "=&v"(n2), [n3] "=&v"(n3)
+        if constexpr (RE_FIRST) {
+#define SV_BODY(MUL, FMA)                                                                                          \
+    "v_mul_f32 %[m0], %[u1], %[ay]\n\tv_mul_f32 %[m1], %[u0], %[ay]\n\t"                                           \
+    "v_mul_f32 %[m2], %[u5], %[ay]\n\tv_mul_f32 %[m3], %[u4], %[ay]\n\t"                                           \
+    "v_mul_f32 %[n0], %[u3], %[by]\n\tv_mul_f32 %[n1], %[u2], %[by]\n\t"                                           \
+    "v_mul_f32 %[n2], %[u7], %[by]\n\tv_mul_f32 %[n3], %[u6], %[by]\n\t"                                           \
+    "v_fma_f32 %[m0], %[u0], %[ax], -%[m0]\n\tv_fmac_f32 %[m1], %[u1], %[ax]\n\t"                                  \
+    "v_fma_f32 %[m2], %[u4], %[ax], -%[m2]\n\tv_fmac_f32 %[m3], %[u5], %[ax]\n\t"                                  \
+    "v_fma_f32 %[n0], %[u2], %[bx], -%[n0]\n\tv_fmac_f32 %[n1], %[u3], %[bx]\n\t"                                  \
+    "v_fma_f32 %[n2], %[u6], %[bx], -%[n2]\n\tv_fmac_f32 %[n3], %[u7], %[bx]\n\t"                                  \
+    "v_add_f32 %[ax], %[m0], %[n0]\n\tv_add_f32 %[ay], %[m1], %[n1]\n\t"                                           \
+    "v_add_f32 %[bx], %[m2], %[n2]\n\tv_add_f32 %[by], %[m3], %[n3]"
+            SV_IP(SV_BODY, SV_OUT8, SV_IN)
+#undef SV_BODY
+        } else {
 #define SV_BODY(MUL, FMA)                                                                                          \
     "v_mul_f32 %[m0], %[u1], %[ay]\n\tv_mul_f32 %[m1], %[u1], %[ax]\n\t"                                           \
     "v_mul_f32 %[m2], %[u5], %[ay]\n\tv_mul_f32 %[m3], %[u5], %[ax]\n\t"                                           \
@@ -164,10 +182,10 @@ __device__ __forceinline__ void pair_ip(const T* u, V& a, V& b, uint64_t ok)
     "v_fma_f32 %[n2], %[u6], %[bx], -%[n2]\n\tv_fmac_f32 %[n3], %[u6], %[by]\n\t"                                  \
     "v_add_f32 %[ax], %[m0], %[n0]\n\tv_add_f32 %[ay], %[m1], %[n1]\n\t"                                           \
     "v_add_f32 %[bx], %[m2], %[n2]\n\tv_add_f32 %[by], %[m3], %[n3]"
-#define SV_OUT8 SV_OUT, [n0] "=&v"(n0), [n1] "=&v"(n1), [n2] "=&v"(n2), [n3] "=&v"(n3)
-        SV_IP(SV_BODY, SV_OUT8, SV_IN)
-#undef SV_OUT8
+            SV_IP(SV_BODY, SV_OUT8, SV_IN)
 #undef SV_BODY
+        }
+#undef SV_OUT8
     }
 #undef SV_IN
 }
@@ -620,11 +638,12 @@ __device__ __forceinline__ bool skip_reg(int j, uint32_t cmk)
 template <typename T, int RB, int K, bool CHK, int M>
 __device__ __forceinline__ void rpair_k(typename Vec2<T>::type* v, const T* u, uint32_t cmk, uint64_t ok)
 {
+    constexpr bool kReFirst = M == IP_MASK;  // the order lane-controlled complex64 pairs have always rounded in
 #pragma unroll
     for (int j = 0; j < (1 << RB); ++j) {
         if (j & (1 << K)) continue;
         if (CHK && skip_reg(j, cmk)) continue;
-        pair_ip<T, M>(u, v[j], v[j | (1 << K)], ok);
+        pair_ip<T, M, kReFirst>(u, v[j], v[j | (1 << K)], ok);
     }
 }
 
