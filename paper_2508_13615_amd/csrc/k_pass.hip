@@ -1100,11 +1100,6 @@ __device__ __forceinline__ void lds_op(typename Vec2<T>::type* v, typename Vec2<
     __syncthreads();
 }
 
-// A workgroup may have more threads than a circuit's tile needs (a batch's
-// circuits share one launch shape): thread i past them repeats the work of
-// thread i mod 2^(tq - rb) on its own registers and writes nothing, so the
-// registers are never under a divergent branch, which would copy all of them
-// at its join.
 // Reads [p, p + bytes) into the scalar cache, one word per 64-byte line,
 // eight lines in flight.  A pass reads each descriptor, layout and coefficient
 // once per wave; in a launch of few workgroups nobody has read them before,
@@ -1124,6 +1119,12 @@ __device__ __forceinline__ void warm_lines(const void* p, int bytes)
 // Workgroups of a launch up to which they warm the scalar cache.
 constexpr uint32_t kWarmGrid = 4096;
 
+// A workgroup may have more threads than a circuit's tile needs (a batch's
+// circuits share one launch shape): thread i past them repeats the work of
+// thread i mod 2^(tq - rb) on its own registers and writes nothing, so the
+// registers are never under a divergent branch, which would copy all of them
+// at its join.
+//
 // GATED: the pass holds one-target ops with controls outside the tile, which
 // act only on the tiles that hold those bits; passes without them take a
 // kernel that does not test for it.

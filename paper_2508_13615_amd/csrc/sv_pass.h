@@ -94,7 +94,7 @@ struct FOp {
     // FK_PAIRC), and cm split into its
     // register bits (as register indices, cmk) and its lane bits (cml).  The
     // planner's lists hold lane bits as tile-local bits; the device's copy
-    // (thread_bits) holds them as bits of the thread index: cml, and a (DIAG,
+    // (device_ops) holds them as bits of the thread index: cml, and a (DIAG,
     // PHASE) or b (PAIRC) where ka or kb is -1.
     int8_t ka, kb;
     uint8_t cmk;

@@ -26,9 +26,8 @@ line-granular bytes of the gate cases the benchmark launches on it (the case
 list and kernel choice come from bench.py and the library's host-only
 sv_plan_info).  ``engine-bounds`` sets the circuits benchmark's engine runs
 (seconds per run from its bench line, one counter run per circuit holding
-SQ_INSTS_VALU, SQ_INSTS_SALU and SQ_WAVES) against their HBM floor (every
-forward pass reads and writes the state once, the observable pass reads it:
-(2 passes + 1) S at 8 TB/s) and their VALU issue floor (a wave64 VALU
+SQ_INSTS_VALU, SQ_INSTS_SALU and SQ_WAVES) against their HBM floor (the bytes
+the plan's passes load and store, at 8 TB/s) and their VALU issue floor (a wave64 VALU
 instruction takes 4 cycles of a 16-lane SIMD; 1024 SIMDs at 2.4 GHz); the
 benchmark runs each circuit 4 times (a warm-up and 3 timed runs), so counter
 totals are divided by 4.  Pass and layout counts come from the library's
