@@ -2,7 +2,8 @@
 
 The call then walks op by op (values as ever) and tries the engine again at the next call: once the memory is free the
 circuit runs on the engine, which shows in the gradient partials it keeps.  The engine is made to need much: tiles of
-2^6 amplitudes on 26 qubits, so that one pass of 60 parameterised gates has 480 MiB of partials.
+2^6 amplitudes on 27 qubits, so that one pass of 60 parameterised gates has 960 MiB of partials (the runtime may give
+back some hundred MiB of its own when memory runs out).
 """
 import numpy as np
 import pytest
@@ -23,12 +24,13 @@ def free_bytes():
 
 
 def test_a_full_device_is_not_remembered():
-    n, k = 26, 60
+    n, k = 27, 60
     ops = [Op(("RX", "RY")[(i // 6) % 2], (), (i % 6,), i) for i in range(k)]
     th = W.uniform_angles(k, 4)
     psi, lam = sv.State(n), sv.State(n)
-    circ, small = sv.Circuit(n, ops, k), sv.Circuit(2, ops[:2], 2)
-    small.adjoint_grad(sv.State(2), sv.State(2), th[:2], W.sum_z(2))  # what the first gradient in a process sets up
+    circ = sv.Circuit(n, ops, k)
+    for m in (2, 20):  # what the first gradient of either form sets up in a process
+        sv.Circuit(6, ops[:m], m).adjoint_grad(sv.State(6), sv.State(6), th[:m], W.sum_z(6))
     tuned = sv.tune_engine_get("c128", True)
     sv.tune_engine_set("c128", True, 6, 8)
     filler = []
@@ -43,7 +45,7 @@ def test_a_full_device_is_not_remembered():
         torch.cuda.empty_cache()
         left = free_bytes()
         e1, g1 = circ.adjoint_grad(psi, lam, th, W.sum_z(n))
-        assert left - free_bytes() > 400 * MiB  # the engine's partials
+        assert left - free_bytes() > 800 * MiB  # the engine's partials
     finally:
         sv.tune_engine_set("c128", True, *tuned)
         filler.clear()
