@@ -113,14 +113,28 @@ __device__ __forceinline__ void small_rx(T c, T m, V a, V b, V& r, V& q)  // m =
     q.y = small_fma(m, a.x, c * b.y);
 }
 
+// The p-th index that holds every bit of cm.
+__device__ __forceinline__ uint32_t small_with(uint32_t p, uint32_t cm)
+{
+    for (; cm; cm &= cm - 1u) {
+        const uint32_t b = cm & (~cm + 1u);
+        p = ((p & ~(b - 1u)) << 1) | b | (p & (b - 1u));
+    }
+    return p;
+}
+
 // A circuit on a state that fits a workgroup's LDS (SmallProgram): the state
 // is read and written once and a gate costs an LDS sweep and a barrier, 1.3 us
 // at 13 qubits complex64, where a launch per gate costs 3.7 us however small
 // the state is (65 gates and the Ising energy: 300 -> 131 us).  What bounds
 // it: vector issue on the one CU (about 30 instructions a pair); grouping
 // gates by target to sweep the LDS less often cost more instructions and
-// measured slower (59 against 43 us for half of those gates).  Larger states,
-// which fill the chip gate by gate, do not come here.
+// measured slower (59 against 43 us for half of those gates).  A run of
+// diagonal gates (a fused circuit's) is one sweep that sums the angles of each
+// amplitude, from 4 terms on with a sincospi each; up to 3 terms it selects
+// from the phases of their combinations (six runs of 2 terms, 13 qubits
+// complex128 33.5 us instead of 42.5).  Larger states, which fill the chip gate
+// by gate, do not come here.
 template <typename T>
 __global__ void __launch_bounds__(kSmallThreads)
 k_small_circuit(typename Vec2<T>::type* __restrict__ psi, int n, SmallProgram prog)
@@ -185,6 +199,79 @@ k_small_circuit(typename Vec2<T>::type* __restrict__ psi, int n, SmallProgram pr
             });
             break;
         case kSmallOne + ONE_MUL: ones([&](V a) { return small_mul(c.m[0], c.m[1], a); }); break;
+        case kSmallPhases: {
+            // Four amplitudes at a time share each term's scalar loads.  The
+            // angles add up in double, also in complex64, whose phase is
+            // rounded once.
+            const uint32_t cnt = na >> __popc(cm);
+            const int nt = op.t;
+            for (uint32_t p0 = tid; p0 < cnt; p0 += 4 * kSmallThreads) {
+                uint32_t x[4];
+                double th[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    x[j] = small_with(p0 + (uint32_t)j * kSmallThreads, cm);
+                    th[j] = 0.0;
+                }
+                for (int t = 0; t < nt; ++t) {
+                    const SmallOp& e = prog.op[k + 1 + (t >> 2)];
+                    const double a = e.m[t & 3];
+                    const uint32_t m = (uint32_t)__double2loint(e.m[4 + (t & 3)]);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) th[j] += (x[j] & m) == m ? a : 0.0;
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (p0 + (uint32_t)j * kSmallThreads >= cnt) break;
+                    T sn, cs;
+                    if constexpr (sizeof(T) == 8) sincospi(th[j], &sn, &cs);
+                    else sincospif((float)(th[j] - 2.0 * rint(0.5 * th[j])), &sn, &cs);
+                    const V a = A[x[j]];
+                    V r;
+                    r.x = small_fma(cs, a.x, -(sn * a.y));
+                    r.y = small_fma(cs, a.y, sn * a.x);
+                    A[x[j]] = r;
+                }
+            }
+            k += (nt + 3) / 4;
+            break;
+        }
+        case kSmallPhaseTable: {
+            const uint32_t cnt = na >> __popc(cm);
+            const uint32_t m0 = (uint32_t)__double2loint(op.m[0]), m1 = (uint32_t)__double2loint(op.m[1]),
+                           m2 = (uint32_t)__double2loint(op.m[2]);
+            T z[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) z[i] = (T)prog.op[k + 1 + (i >> 3)].m[i & 7];
+            constexpr int U = sizeof(T) == 4 ? 4 : 1;  // complex128: 33.5 us at one a time, 41.5 at four (six runs, 13 qubits)
+            for (uint32_t p0 = tid; p0 < cnt; p0 += U * kSmallThreads) {
+                uint32_t x[U];
+                V a[U];
+#pragma unroll
+                for (int j = 0; j < U; ++j) {
+                    const uint32_t p = p0 + (uint32_t)j * kSmallThreads;
+                    x[j] = small_with(p < cnt ? p : p0, cm);
+                    a[j] = A[x[j]];
+                }
+#pragma unroll
+                for (int j = 0; j < U; ++j) {
+                    const bool b0 = (x[j] & m0) == m0, b1 = (x[j] & m1) == m1, b2 = (x[j] & m2) == m2;
+                    T w[4];  // by the first two, for either value of the third
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int h = 8 * (i >> 1) + (i & 1);
+                        w[i] = b1 ? (b0 ? z[h + 6] : z[h + 4]) : (b0 ? z[h + 2] : z[h]);
+                    }
+                    const T cs = b2 ? w[2] : w[0], sn = b2 ? w[3] : w[1];
+                    V r;
+                    r.x = small_fma(cs, a[j].x, -(sn * a[j].y));
+                    r.y = small_fma(cs, a[j].y, sn * a[j].x);
+                    if (p0 + (uint32_t)j * kSmallThreads < cnt) A[x[j]] = r;
+                }
+            }
+            k += 2;
+            break;
+        }
         default: {  // two targets
             const uint32_t ub = 1u << op.u;
             const int lo = op.t < op.u ? op.t : op.u, hi = op.t < op.u ? op.u : op.t;

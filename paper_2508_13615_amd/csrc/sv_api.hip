@@ -1555,10 +1555,6 @@ static sv_status circuit_forward(sv_circuit c, sv_state st, const double* params
 
 // Whether a circuit's gates run in one workgroup (k_small_circuit): the state
 // fits its LDS, and there is more than one gate to share the round trip.
-// sv_circuit_apply only: this form applies and rounds every gate by itself,
-// while sv_circuit_apply_fused sums a diagonal run's angles first (and is the
-// faster of the two on such runs: 40 phases on 13 qubits complex128 7 us in
-// one pass, 57 us here).
 // On 2^14 amplitudes (complex64) loading and storing the state takes one
 // workgroup about 5 us and a 4x4 gate's sweep 4.3 us, as much as its own
 // launch, so the circuit needs three gates that are not 4x4 (us, launched /
@@ -1575,29 +1571,60 @@ static bool small_circuit(const sv_circuit_s* c, const sv_state_s* st)
     return light >= kLightOps;
 }
 
-static sv_status circuit_forward_small(sv_circuit c, sv_state st, const double* params)
+// exp(i pi turns), exact at quarter turns.
+static void half_turns(double turns, double* z)
 {
+    const double r = turns - 2.0 * rint(0.5 * turns);
+    const double q = 2.0 * r;
+    if (q == rint(q)) {
+        const int k = ((int)q + 4) % 4;
+        z[0] = k == 0 ? 1.0 : k == 2 ? -1.0 : 0.0;
+        z[1] = k == 1 ? 1.0 : k == 3 ? -1.0 : 0.0;
+        return;
+    }
+    z[0] = cos(M_PI * r);
+    z[1] = sin(M_PI * r);
+}
+
+constexpr int kSmallTableTerms = 3;  // of a phase run whose phases fit kSmallPhaseTable
+
+// Gates for k_small_circuit, a launch per kSmallOps entries.
+struct SmallCircuit {
+    sv_circuit c;
+    sv_state st;
+    const double* params;
     SmallProgram prog;
-    prog.n_ops = prog.pad = 0;
-    auto flush = [&]() {
+
+    sv_status flush()
+    {
         if (!prog.n_ops) return SV_OK;
         const hipError_t e = st->dtype == SV_C128 ? launch_small_circuit<double>(st->data, st->n, prog, st->stream)
                                                   : launch_small_circuit<float>(st->data, st->n, prog, st->stream);
         prog.n_ops = 0;
         return hip_status(e, "small circuit launch");
-    };
-    for (const OpRec& o : c->ops) {
-        Plan pl;
-        sv_status rc = op_plan(c, st->dtype, o, params, 0, &pl);
-        if (rc) return rc;
-        if (pl.kind == PK_NOP) continue;
-        const int entries = o.gate == SV_U4 ? 4 : 1;
+    }
+
+    // Room for `entries` zeroed entries, in the next launch if need be.
+    sv_status room(int entries, SmallOp** so)
+    {
         if (prog.n_ops + entries > kSmallOps) {
-            rc = flush();
+            const sv_status rc = flush();
             if (rc) return rc;
         }
-        SmallOp* so = &prog.op[prog.n_ops];
-        memset(so, 0, sizeof(SmallOp) * entries);
+        *so = &prog.op[prog.n_ops];
+        memset(*so, 0, sizeof(SmallOp) * entries);
+        prog.n_ops += entries;
+        return SV_OK;
+    }
+
+    sv_status gate(const OpRec& o)
+    {
+        Plan pl;
+        sv_status rc = op_plan(c, st->dtype, o, params, 0, &pl);
+        if (rc || pl.kind == PK_NOP) return rc;
+        SmallOp* so;
+        rc = room(o.gate == SV_U4 ? 4 : 1, &so);
+        if (rc) return rc;
         for (int j = 0; j < o.nc; ++j) so->cm |= 1u << o.q[j];
         so->t = (uint8_t)o.q[o.nc];
         if (o.gate == SV_U4 || o.gate == SV_SWAP) {
@@ -1613,9 +1640,81 @@ static sv_status circuit_forward_small(sv_circuit c, sv_state st, const double* 
             so->kind = (uint8_t)pl.op;
             memcpy(so->m, pl.m, sizeof so->m);
         }
-        prog.n_ops += entries;
+        return SV_OK;
     }
-    return flush();
+
+    // The phases of a run (at most kMaxPhaseTerms), terms on one mask summed.
+    sv_status phases(const std::vector<uint64_t>& masks, const std::vector<double>& turns)
+    {
+        uint32_t mask[kMaxPhaseTerms], common = ~0u;
+        double sum[kMaxPhaseTerms];
+        int nt = 0;
+        for (size_t t = 0; t < masks.size(); ++t) {
+            int k = 0;
+            while (k < nt && mask[k] != (uint32_t)masks[t]) ++k;
+            if (k == nt) {
+                mask[nt] = (uint32_t)masks[t];
+                sum[nt++] = 0.0;
+            }
+            sum[k] += turns[t];
+            common &= (uint32_t)masks[t];
+        }
+        // a term that asks for no further bit is part of every amplitude's angle
+        double base = 0.0;
+        int k = 0;
+        for (int t = 0; t < nt; ++t) {
+            if (const uint32_t rest = mask[t] & ~common) {
+                mask[k] = rest;
+                sum[k++] = sum[t];
+            } else {
+                base += sum[t];
+            }
+        }
+        SmallOp* so;
+        if (k <= kSmallTableTerms) {
+            const sv_status rc = room(3, &so);
+            if (rc) return rc;
+            so->kind = kSmallPhaseTable;
+            so->cm = common;
+            for (int t = 0; t < kSmallTableTerms; ++t) {
+                const uint64_t w = t < k ? mask[t] : 0;
+                memcpy(&so->m[t], &w, sizeof w);
+            }
+            for (int i = 0; i < 1 << kSmallTableTerms; ++i) {
+                double th = base;
+                for (int t = 0; t < k; ++t)
+                    if ((i >> t) & 1) th += sum[t];
+                half_turns(th, &so[1 + i / 4].m[2 * (i % 4)]);
+            }
+            return SV_OK;
+        }
+        if (base != 0.0) {
+            mask[k] = 0;
+            sum[k++] = base;
+        }
+        const sv_status rc = room(1 + (k + 3) / 4, &so);
+        if (rc) return rc;
+        so->kind = kSmallPhases;
+        so->cm = common;
+        so->t = (uint8_t)k;
+        for (int t = 0; t < k; ++t) {
+            SmallOp& e = so[1 + t / 4];
+            const uint64_t w = mask[t];
+            e.m[t % 4] = sum[t];
+            memcpy(&e.m[4 + t % 4], &w, sizeof w);
+        }
+        return SV_OK;
+    }
+};
+
+static sv_status circuit_forward_small(sv_circuit c, sv_state st, const double* params)
+{
+    SmallCircuit sc{c, st, params, {}};
+    for (const OpRec& o : c->ops) {
+        const sv_status rc = sc.gate(o);
+        if (rc) return rc;
+    }
+    return sc.flush();
 }
 
 // ---- runs of diagonal gates -------------------------------------------------
@@ -1697,9 +1796,11 @@ static bool pair_fusable(const OpRec& o)
 // The circuit with every run of two or more consecutive diagonal ops applied
 // as one phase pass (a run longer than kMaxPhaseTerms terms takes several),
 // consecutive uncontrolled one-target gates on one qubit composed into one
-// 2x2, and such a gate followed by a diagonal run applied together with it
-// in one pass.
-static sv_status circuit_forward_fused(sv_circuit c, sv_state st, const double* params)
+// 2x2, and such a gate followed by a diagonal run applied together with it.
+// E applies what is found: gate(op), run(masks, turns), and pair_run(op, its
+// 2x2, the run's first op if that is all of it, masks, turns).
+template <typename E>
+static sv_status fused_walk(sv_circuit c, const double* params, E& ex)
 {
     std::vector<uint64_t> masks;
     std::vector<double> turns;
@@ -1707,89 +1808,28 @@ static sv_status circuit_forward_fused(sv_circuit c, sv_state st, const double* 
     int pending = -1;  // a pair gate waiting for the run after it
     std::vector<std::complex<double>> pend;  // its matrix, later same-qubit gates composed on
     int pend_ops = 0;                        // ops composed into pend
-    auto run_op = [&](const OpRec& o) -> sv_status {
-        Plan pl;
-        sv_status rc = op_plan(c, st->dtype, o, params, 0, &pl);
-        if (!rc) rc = run_plan(pl, st, st->data);
-        return rc;
-    };
     auto flush = [&]() -> sv_status {
         sv_status rc = SV_OK;
         if (pending >= 0) {
-            if (masks.empty()) {
-                if (pend_ops == 1) {
-                    rc = run_op(c->ops[pending]);
-                } else {  // the composed 2x2 as a U2 on the same qubit
-                    OpRec u2 = c->ops[pending];
-                    u2.gate = SV_U2;
-                    u2.pidx = -1;
-                    u2.matrix.resize(8);
-                    for (int e = 0; e < 4; ++e) {
-                        u2.matrix[2 * e] = pend[e].real();
-                        u2.matrix[2 * e + 1] = pend[e].imag();
-                    }
-                    rc = run_op(u2);
-                }
-            } else {
-                PairCoef u;
+            const OpRec* g = &c->ops[pending];
+            OpRec u2;
+            if (pend_ops > 1) {  // the composed 2x2 as a U2 on the same qubit
+                u2 = *g;
+                u2.gate = SV_U2;
+                u2.pidx = -1;
+                u2.matrix.resize(8);
                 for (int e = 0; e < 4; ++e) {
-                    u.m[2 * e] = pend[e].real();
-                    u.m[2 * e + 1] = pend[e].imag();
+                    u2.matrix[2 * e] = pend[e].real();
+                    u2.matrix[2 * e + 1] = pend[e].imag();
                 }
-                const uint64_t tb = 1ull << c->ops[pending].q[0];
-                // every term holds the gate's qubit and at most one more bit: a
-                // phase linear in the bits, tabulated per byte by the kernel
-                bool linear = true;
-                for (uint64_t m2 : masks) linear &= (m2 & tb) && __builtin_popcountll(m2 & ~tb) <= 1;
-                if (linear) {
-                    LinearPhase lp;
-                    memset(&lp, 0, sizeof lp);
-                    int top = 0;
-                    for (size_t t = 0; t < masks.size(); ++t) {
-                        const uint64_t other = masks[t] & ~tb;
-                        if (!other) {
-                            lp.turns_const += turns[t];
-                            continue;
-                        }
-                        const int b = __builtin_ctzll(other);
-                        lp.turns_of_bit[b] += turns[t];
-                        top = std::max(top, b);
-                    }
-                    lp.n_bytes = top / 8 + 1;
-                    // the per-byte phase tables live in the state's workspace
-                    rc = ensure_work(st, kLinearPhaseTableBytes / sizeof(double));
-                    if (!rc)
-                        rc = hip_status(launch_pair_linear_phase(st->data, st->dtype, c->ops[pending].q[0], u, lp,
-                                                                 (int64_t)1 << (st->n - 1), st->work + kWorkHead,
-                                                                 st->stream),
-                                        "pair and linear phase launch");
-                    masks.clear();
-                    turns.clear();
-                    run_len = 0;
-                    pending = -1;
-                    return rc;
-                }
-                // terms holding the gate's qubit first (they reach only its 1 side)
-                PhaseRun pr;
-                memset(&pr, 0, sizeof pr);
-                int n_with = 0;
-                for (int pass = 0; pass < 2; ++pass)
-                    for (size_t t = 0; t < masks.size(); ++t)
-                        if (((masks[t] & tb) != 0) == (pass == 0)) {
-                            pr.mask[pr.n_terms] = masks[t];
-                            pr.turns[pr.n_terms] = turns[t];
-                            ++pr.n_terms;
-                            n_with += pass == 0;
-                        }
-                pr.groups = (int64_t)1 << (st->n - 1);
-                rc = hip_status(
-                    launch_pair_phase_run(st->data, st->dtype, c->ops[pending].q[0], u, pr, n_with, st->stream),
-                    "pair and phase run launch");
+                g = &u2;
             }
+            if (masks.empty()) rc = ex.gate(*g);
+            else rc = ex.pair_run(*g, pend, run_len == 1 ? &c->ops[run_begin] : nullptr, masks, turns);
         } else if (run_len == 1) {  // a lone diagonal op keeps its own kernel
-            rc = run_op(c->ops[run_begin]);
+            rc = ex.gate(c->ops[run_begin]);
         } else if (!masks.empty()) {
-            rc = run_phase_terms(st, masks.data(), turns.data(), (int)masks.size());
+            rc = ex.run(masks, turns);
         }
         masks.clear();
         turns.clear();
@@ -1830,10 +1870,184 @@ static sv_status circuit_forward_fused(sv_circuit c, sv_state st, const double* 
             pend_ops = 1;
             continue;
         }
-        rc = run_op(o);
+        rc = ex.gate(o);
         if (rc) return rc;
     }
     return flush();
+}
+
+// A launch per gate or run.
+struct FusedLaunch {
+    sv_circuit c;
+    sv_state st;
+    const double* params;
+
+    sv_status gate(const OpRec& o)
+    {
+        Plan pl;
+        sv_status rc = op_plan(c, st->dtype, o, params, 0, &pl);
+        if (!rc) rc = run_plan(pl, st, st->data);
+        return rc;
+    }
+
+    sv_status run(const std::vector<uint64_t>& masks, const std::vector<double>& turns)
+    {
+        return run_phase_terms(st, masks.data(), turns.data(), (int)masks.size());
+    }
+
+    // One pass over the pairs of the gate's qubit.
+    sv_status pair_run(const OpRec& g, const std::vector<std::complex<double>>& pend, const OpRec*,
+                       const std::vector<uint64_t>& masks, const std::vector<double>& turns)
+    {
+        const int q = g.q[0];
+        const uint64_t tb = 1ull << q;
+        PairCoef u;
+        for (int e = 0; e < 4; ++e) {
+            u.m[2 * e] = pend[e].real();
+            u.m[2 * e + 1] = pend[e].imag();
+        }
+        // every term holds the gate's qubit and at most one more bit: a
+        // phase linear in the bits, tabulated per byte by the kernel
+        bool linear = true;
+        for (uint64_t m2 : masks) linear &= (m2 & tb) && __builtin_popcountll(m2 & ~tb) <= 1;
+        if (linear) {
+            LinearPhase lp;
+            memset(&lp, 0, sizeof lp);
+            int top = 0;
+            for (size_t t = 0; t < masks.size(); ++t) {
+                const uint64_t other = masks[t] & ~tb;
+                if (!other) {
+                    lp.turns_const += turns[t];
+                    continue;
+                }
+                const int b = __builtin_ctzll(other);
+                lp.turns_of_bit[b] += turns[t];
+                top = std::max(top, b);
+            }
+            lp.n_bytes = top / 8 + 1;
+            // the per-byte phase tables live in the state's workspace
+            const sv_status rc = ensure_work(st, kLinearPhaseTableBytes / sizeof(double));
+            if (rc) return rc;
+            return hip_status(launch_pair_linear_phase(st->data, st->dtype, q, u, lp, (int64_t)1 << (st->n - 1),
+                                                       st->work + kWorkHead, st->stream),
+                              "pair and linear phase launch");
+        }
+        // terms holding the gate's qubit first (they reach only its 1 side)
+        PhaseRun pr;
+        memset(&pr, 0, sizeof pr);
+        int n_with = 0;
+        for (int pass = 0; pass < 2; ++pass)
+            for (size_t t = 0; t < masks.size(); ++t)
+                if (((masks[t] & tb) != 0) == (pass == 0)) {
+                    pr.mask[pr.n_terms] = masks[t];
+                    pr.turns[pr.n_terms] = turns[t];
+                    ++pr.n_terms;
+                    n_with += pass == 0;
+                }
+        pr.groups = (int64_t)1 << (st->n - 1);
+        return hip_status(launch_pair_phase_run(st->data, st->dtype, q, u, pr, n_with, st->stream),
+                          "pair and phase run launch");
+    }
+};
+
+// All of it in one workgroup: the composed 2x2s as gates, the runs as angles
+// summed per amplitude.
+struct FusedSmall {
+    SmallCircuit sc;
+    sv_status gate(const OpRec& o) { return sc.gate(o); }
+    sv_status run(const std::vector<uint64_t>& masks, const std::vector<double>& turns) { return sc.phases(masks, turns); }
+    sv_status pair_run(const OpRec& g, const std::vector<std::complex<double>>&, const OpRec* lone,
+                       const std::vector<uint64_t>& masks, const std::vector<double>& turns)
+    {
+        const sv_status rc = sc.gate(g);
+        if (rc) return rc;
+        return lone ? sc.gate(*lone) : sc.phases(masks, turns);
+    }
+};
+
+// Whether a fused circuit takes the one workgroup: its time there against a
+// launch per pass (3.9 us each on a small state, two where a linear run's
+// phase tables come first), both estimated gate by gate as fused_walk will
+// group them.  Measured on one CU, with a = amplitudes a thread holds: a gate
+// 0.5 us + 0.135 a (complex64 0.1), a 4x4 gate 0.5 + 0.3 a, a run of nt terms
+// 0.4 + 0.55 a (0.3) + 0.155 nt for each four amplitudes.  Launched / here, us:
+// QFT of 13 qubits complex128 95 / 68, 14 qubits complex64 106 / 106, 10 qubits
+// 70 / 22; four HEA layers on 13 qubits complex128 407 / 244; six H and runs of
+// 8 phases on 10 qubits 25.1 / 20.0, on 13 qubits 24.5 / 53.9; 40 phases alone
+// on 13 qubits 6.8 / 19.1, which stay launched.
+static bool fused_small(const sv_circuit_s* c, const sv_state_s* st)
+{
+    if (c->ops.size() < 2 || (elem_bytes(st->dtype) << st->n) > kSmallStateBytes) return false;
+    const bool wide = st->dtype == SV_C128;
+    constexpr double kLaunch = 3.9;
+    constexpr int kSearch = 16;  // masks up to which a run's terms are looked for among them
+    const double a = std::max(1.0, (double)(1ull << st->n) / kSmallThreads);
+    const double gate = 0.5 + (wide ? 0.135 : 0.1) * a, quad = 0.5 + 0.3 * a;
+    double here = kLaunch + 0.1 * a, launched = 0.0;
+    uint64_t mask[kMaxPhaseTerms];
+    int nt = 0, terms = 0, len = 0, pend = -1;  // distinct and all terms of the run, its ops, the qubit of the gate before it
+    auto flush = [&] {
+        double passes = pend >= 0 || len > 0 ? 1.0 : 0.0;
+        if (pend >= 0) here += gate;
+        if (len == 1) here += gate;
+        if (len > 0) {
+            uint64_t common = ~0ull;
+            bool linear = pend >= 0;
+            for (int t = 0; t < nt; ++t) {
+                common &= mask[t];
+                if (pend >= 0)
+                    linear &= ((mask[t] >> pend) & 1) && __builtin_popcountll(mask[t] & ~(1ull << pend)) <= 1;
+            }
+            if (linear) passes = 2.0;
+            if (len > 1) {
+                const double b = std::max(1.0, a / (double)(1ull << __builtin_popcountll(common)));
+                int k = 0;
+                for (int t = 0; t < nt; ++t) k += (mask[t] & ~common) != 0;
+                here += k <= kSmallTableTerms ? 0.5 + (wide ? 0.2 : 0.12) * b
+                                              : 0.4 + (wide ? 0.55 : 0.3) * b + 0.155 * nt * ceil(b / 4);
+            }
+        }
+        launched += kLaunch * passes;
+        nt = terms = len = 0;
+        pend = -1;
+    };
+    for (const OpRec& o : c->ops) {
+        uint64_t controls = 0;
+        for (int j = 0; j < o.nc; ++j) controls |= 1ull << o.q[j];
+        const bool rz = o.gate == SV_RZ;
+        if (rz || o.gate == SV_Z || o.gate == SV_S || o.gate == SV_T || o.gate == SV_PHASE || o.gate == SV_I) {
+            uint64_t m[2] = {controls | 1ull << o.q[o.nc], controls};
+            const int k = o.gate == SV_I ? 0 : rz ? 2 : 1;
+            if (terms + k > kMaxPhaseTerms) flush();
+            ++len;
+            terms += k;
+            for (int j = 0; j < k; ++j)
+                if (nt >= kSearch || std::find(mask, mask + nt, m[j]) == mask + nt) mask[nt++] = m[j];
+            continue;
+        }
+        const bool pair = pair_fusable(o);
+        if (pair && pend == o.q[0] && len == 0) continue;
+        flush();
+        if (pair) {
+            pend = o.q[0];
+        } else {
+            here += o.gate == SV_U4 ? quad : gate;
+            launched += kLaunch;
+        }
+    }
+    flush();
+    return here <= launched;
+}
+
+static sv_status circuit_forward_fused(sv_circuit c, sv_state st, const double* params)
+{
+    if (fused_small(c, st)) {
+        FusedSmall ex{{c, st, params, {}}};
+        const sv_status rc = fused_walk(c, params, ex);
+        return rc ? rc : ex.sc.flush();
+    }
+    FusedLaunch ex{c, st, params};
+    return fused_walk(c, params, ex);
 }
 
 sv_status sv_circuit_apply_fused(sv_circuit c_h, sv_state st_h, const double* params)

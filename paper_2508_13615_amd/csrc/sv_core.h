@@ -213,12 +213,20 @@ constexpr int kSmallThreads = 1024;
 enum SmallKind : int {  // PairOp values below kSmallOne, then OneOp values, then two-target gates
     kSmallOne = 8,
     kSmallSwap = 16,
-    kSmallQuad = 17  // 4x4: the coefficients run on through the next 3 entries
+    kSmallQuad = 17,  // 4x4: the coefficients run on through the next 3 entries
+    // A run of t phases on the amplitudes holding cm, summed as angles: the
+    // next entries hold 4 terms each, m[j] the angle in half-turns and the low
+    // word of m[4 + j] the further bits that the term asks for.
+    kSmallPhases = 18,
+    // A run of at most 3 phases on the amplitudes holding cm: the low words of
+    // m[0..2] are the further bits that each asks for, and the next 2 entries
+    // hold the phase of every combination of them.
+    kSmallPhaseTable = 19
 };
 struct SmallOp {
     uint32_t cm;       // bits that must all be 1
     uint8_t kind;
-    uint8_t t, u;      // target bits (matrix: t is the most significant)
+    uint8_t t, u;      // target bits (matrix: t is the most significant); t: the terms of a phase run
     uint8_t pad;
     double m[8];
 };
