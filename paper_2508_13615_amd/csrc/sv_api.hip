@@ -1804,6 +1804,8 @@ static sv_status fused_walk(sv_circuit c, const double* params, E& ex)
 {
     std::vector<uint64_t> masks;
     std::vector<double> turns;
+    std::vector<uint64_t> m;  // of one op
+    std::vector<double> tt;
     size_t run_begin = 0, run_len = 0;
     int pending = -1;  // a pair gate waiting for the run after it
     std::vector<std::complex<double>> pend;  // its matrix, later same-qubit gates composed on
@@ -1839,8 +1841,8 @@ static sv_status fused_walk(sv_circuit c, const double* params, E& ex)
     };
     for (size_t i = 0; i < c->ops.size(); ++i) {
         const OpRec& o = c->ops[i];
-        std::vector<uint64_t> m;
-        std::vector<double> tt;
+        m.clear();
+        tt.clear();
         if (diag_terms(o, params, m, tt)) {
             if (masks.size() + m.size() > (size_t)kMaxPhaseTerms) {
                 sv_status rc = flush();
@@ -1854,11 +1856,11 @@ static sv_status fused_walk(sv_circuit c, const double* params, E& ex)
         }
         if (pair_fusable(o) && pending >= 0 && run_len == 0 && c->ops[pending].q[0] == o.q[0]) {
             // o after the pending gate on the same qubit: pend <- M(o) pend
-            std::vector<std::complex<double>> m;
-            op_target_matrix(o, params, m);
+            std::vector<std::complex<double>> g;
+            op_target_matrix(o, params, g);
             const std::vector<std::complex<double>> a = pend;
             for (int r = 0; r < 2; ++r)
-                for (int k = 0; k < 2; ++k) pend[2 * r + k] = m[2 * r] * a[k] + m[2 * r + 1] * a[2 + k];
+                for (int k = 0; k < 2; ++k) pend[2 * r + k] = g[2 * r] * a[k] + g[2 * r + 1] * a[2 + k];
             ++pend_ops;
             continue;
         }
@@ -2028,6 +2030,7 @@ static bool fused_small(const sv_circuit_s* c, const sv_state_s* st)
         const bool pair = pair_fusable(o);
         if (pair && pend == o.q[0] && len == 0) continue;
         flush();
+        if (launched > 25 * kLaunch && 2 * here < launched) return true;  // clear: the first launch waits for this scan
         if (pair) {
             pend = o.q[0];
         } else {
